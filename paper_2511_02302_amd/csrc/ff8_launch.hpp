@@ -96,6 +96,17 @@ hipError_t launch_grouped_gemm(GemmMode mode, const uint8_t* a, const e8m0_t* a_
                                const e8m0_t* b_s, const int32_t* offsets, int E, int64_t M_cap, int64_t N,
                                int64_t K, void* out, int accumulate, hipStream_t st);
 
+// The same products on 128 x tq tiles (tq = 64 or 128; wgrad: 128) for small groups, short
+// contractions and small grids; small_gemm_tile gives the tq a product should take, 0 for the
+// 256 x 256 tiles.
+int small_gemm_tile(GemmMode mode, int E, int64_t M_cap, int64_t N, int64_t K);
+hipError_t launch_grouped_gemm_small(GemmMode mode, int tq, const uint8_t* a, const float* a_s, const uint8_t* b,
+                                     const float* b_s, const int32_t* offsets, int E, int64_t M_cap, int64_t N,
+                                     int64_t K, void* out, int accumulate, hipStream_t st);
+hipError_t launch_grouped_gemm_small(GemmMode mode, int tq, const uint8_t* a, const e8m0_t* a_s, const uint8_t* b,
+                                     const e8m0_t* b_s, const int32_t* offsets, int E, int64_t M_cap, int64_t N,
+                                     int64_t K, void* out, int accumulate, hipStream_t st);
+
 // Number of workgroups that fill the device (CU count x `per_cu`), cached per device.
 int device_cu_count();
 

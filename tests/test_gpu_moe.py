@@ -631,3 +631,87 @@ def test_wgrad_tile_schedules(rows):
             assert not got[e].any(), e
         else:
             assert rel_frob(got[e], 2 * want[e]) < GEMM_TOL, e
+
+
+def _codes(rng, shape):
+    return rng.choice(np.r_[0:127, 128:255].astype(np.uint8), size=shape)
+
+
+def _pow2(rng, shape):
+    return np.exp2(rng.integers(-6, 3, size=shape)).astype(np.float32)
+
+
+# Row groups at the edges of the tile shapes the row-wise products choose between (64, 128 or 256
+# rows by 128 or 256 columns), with odd numbers of column tiles and of K blocks.
+ROW_TILE_CASES = {
+    # up to 64 rows per group: one 64-row tile each, more tiles than workgroups run at once, one K block
+    "rows64_many_tiles": ([16, 64, 0, 48, 32, 16, 64, 16], 32768, 128),
+    "rows64_odd": ([16, 64, 0, 48, 32, 16, 64, 16], 640, 384),
+    # up to 96 rows on average: 128-row tiles, groups at and under 128 rows
+    "rows96": ([128, 80, 16, 112, 0, 128, 96, 80], 1152, 640),
+    # few tiles of a longer contraction: a small grid, groups that end inside tiles
+    "small_grid": ([512, 272], 1152, 1024),
+    "small_grid_short": ([256, 144, 16], 640, 256),
+    # enough 256-row tiles for every CU several times over, odd column tiles
+    "large_grid": ([1024, 784], 22144, 384),
+}
+
+
+@pytest.mark.parametrize("case", list(ROW_TILE_CASES))
+@pytest.mark.parametrize("mode", ["fprop", "dgrad"])
+def test_row_tile_shapes(mode, case):
+    """fprop and dgrad over whole outputs at every tile shape; operands are random e4m3 codes with
+    random power-of-two scales, and rows past the groups keep their bytes."""
+    rows, cols, depth = ROW_TILE_CASES[case]
+    E = len(rows)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int64)
+    m = int(off[-1])
+    M_cap = -(-(m + 16) // 128) * 128
+    N, K = (cols, depth) if mode == "fprop" else (depth, cols)
+    rng = np.random.default_rng(m + cols)
+    a, a_s = _codes(rng, (M_cap, depth)), _pow2(rng, (M_cap, depth // 128))
+    w, w_s = _codes(rng, (E, N, K)), _pow2(rng, (E, N // 128, K // 128))
+    out = poisoned((M_cap, cols), torch.bfloat16)
+    args = [dev(torch.from_numpy(x)) for x in (a, a_s, w, w_s, off.astype(np.int32))]
+    getattr(ff8, f"ff8_grouped_gemm_{mode}")(*args, out)
+    torch.cuda.synchronize()
+    want = getattr(moe, f"grouped_gemm_{mode}")(a, a_s, w, w_s, off)
+    for e in range(E):  # every group by itself: a small one must not hide in the norm of the others
+        if rows[e]:
+            assert rel_frob(f64(out[off[e]:off[e + 1]]), want[off[e]:off[e + 1]]) < GEMM_TOL, e
+    assert untouched(out[m:])
+
+
+# Token groups for wgrad: 128 x 128 tiles up to 640 tokens per expert, one or several tiles per
+# workgroup, and 256 x 256 tiles in both XCD orders above.
+TOKEN_CASES = {
+    "short_one_tile_each": ([16, 128, 0, 48], 2048, 2176),
+    "short_empty_first": ([0, 0, 272, 400], 1152, 640),
+    "short_rounds": ([640, 16, 528, 0, 1040, 128], 2048, 1920),
+    "large_skewed": ([6000, 128, 0, 272], 4096, 4096),
+    "large_uniform": ([1024, 912, 1040, 1024], 4096, 4096),
+}
+
+
+@pytest.mark.parametrize("case", list(TOKEN_CASES))
+def test_token_tile_shapes(case):
+    """wgrad over whole outputs at every tile shape, then accumulated into the same gradient."""
+    rows, N, K = TOKEN_CASES[case]
+    E = len(rows)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int64)
+    M_cap = int(-(-off[-1] // 128) * 128)
+    rng = np.random.default_rng(sum(rows) + N)
+    gT, xT = _codes(rng, (N, M_cap)), _codes(rng, (K, M_cap))
+    gTs, xTs = _pow2(rng, (M_cap // 128, N)), _pow2(rng, (M_cap // 128, K))
+    args = [dev(torch.from_numpy(x)) for x in (to_kblock(gT), gTs, to_kblock(xT), xTs, off.astype(np.int32))]
+    dw = torch.full((E, N, K), 7.0, dtype=torch.float32, device="cuda")
+    want = moe.grouped_gemm_wgrad(gT, gTs.T, xT, xTs.T, off)
+    for accumulate in (False, True):
+        ff8.ff8_grouped_gemm_wgrad(*args, dw, accumulate=accumulate)
+        torch.cuda.synchronize()
+        got = host(dw)
+        for e in range(E):
+            if rows[e] == 0:
+                assert not got[e].any(), e
+            else:
+                assert rel_frob(got[e], (1 + accumulate) * want[e]) < GEMM_TOL, e
