@@ -14,6 +14,8 @@
 // (64-token chunks, four times the workgroups, measured the same; four waves per chunk in
 // route_assign instead of one wave walking it 64 tokens at a time saved 6 us of the routing
 // launches' ~26 us at the DeepSeek-V3 share.)
+// The last two are one launch (route_assign_scan) where every chunk can sum the counts for
+// itself, and all three where it can count the pairs for itself.
 // Then permute_quant reads each token row ONCE (one workgroup per token, 16 elements per
 // lane, 8 lanes per 1x128 tile, DPP amax), quantizes it and writes it to each of its k
 // rows; with routing weights each copy is scaled (float32 product) and quantized
@@ -123,25 +125,31 @@ __global__ __launch_bounds__(1024) void route_scan_kernel(int32_t* __restrict__ 
   if (threadIdx.x == 0) offsets[E] = offs[E];
 }
 
-// One workgroup (4 waves) per chunk: wave w takes tokens 64 w .. 64 w + 63 of the chunk and
+// Sum of the 256 threads' values below and including each thread, in thread order (wsum: 4 ints).
+__device__ __forceinline__ int chunk_inclusive_sum(int v, int* wsum) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int u = __shfl_up(v, d);
+    if (lane >= d) v += u;
+  }
+  if (lane == 63) wsum[w] = v;
+  __syncthreads();
+  for (int i = 0; i < w; ++i) v += wsum[i];
+  __syncthreads();  // wsum is reused by the next call
+  return v;
+}
+
+// Rows of a chunk's pairs (4 waves): wave w takes tokens 64 w .. 64 w + 63 of the chunk and
 // sets, per expert, a 64-bit LDS mask of its lanes routed there; a pair's rank is the
 // chunk's base for its expert, plus the popcounts of that expert's masks in earlier waves,
 // plus its position among earlier lanes of its own mask.  All four waves work at once (one
-// round of routing loads per chunk instead of four).
-__global__ __launch_bounds__(kChunk) void route_assign_kernel(const int32_t* __restrict__ idx, int64_t T, int k, int E,
-                                                             const int32_t* __restrict__ bases,
-                                                             int32_t* __restrict__ row_map, int32_t* __restrict__ src_row) {
+// round of routing loads per chunk instead of four).  base, mask: LDS, base set, mask zeroed.
+__device__ __forceinline__ void assign_rows(const int32_t* __restrict__ idx, int64_t chunk, int64_t T, int k, int E,
+                                            const int* base, unsigned long long (*mask)[1024],
+                                            int32_t* __restrict__ row_map, int32_t* __restrict__ src_row) {
   static_assert(kChunk == 256, "four waves of 64 tokens per chunk");
-  __shared__ int run[1024];
-  __shared__ unsigned long long mask[4][1024];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int64_t chunk = blockIdx.x;
-  for (int e = tid; e < E; e += kChunk) {
-    run[e] = bases[chunk * E + e];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) mask[w][e] = 0ull;
-  }
-  __syncthreads();
   const int64_t t = chunk * kChunk + tid;
   const bool valid = t < T;
   for (int j = 0; j < k && valid; ++j) {
@@ -154,7 +162,7 @@ __global__ __launch_bounds__(kChunk) void route_assign_kernel(const int32_t* __r
     const int e = idx[t * k + j];
     int row = -1;
     if (e >= 0 && e < E) {
-      row = run[e] + __popcll(mask[wave][e] & below);
+      row = base[e] + __popcll(mask[wave][e] & below);
       for (int w = 0; w < wave; ++w) row += __popcll(mask[w][e]);
       src_row[row] = (int32_t)(t * k + j);
     }
@@ -162,30 +170,130 @@ __global__ __launch_bounds__(kChunk) void route_assign_kernel(const int32_t* __r
   }
 }
 
+__global__ __launch_bounds__(kChunk) void route_assign_kernel(const int32_t* __restrict__ idx, int64_t T, int k, int E,
+                                                             const int32_t* __restrict__ bases,
+                                                             int32_t* __restrict__ row_map, int32_t* __restrict__ src_row) {
+  __shared__ int run[1024];
+  __shared__ unsigned long long mask[4][1024];
+  const int64_t chunk = blockIdx.x;
+  for (int e = threadIdx.x; e < E; e += kChunk) {
+    run[e] = bases[chunk * E + e];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) mask[w][e] = 0ull;
+  }
+  __syncthreads();
+  assign_rows(idx, chunk, T, k, E, run, mask, row_map, src_row);
+}
+
+// The scan and the assignment in one launch, for routings small enough that every chunk's
+// workgroup can sum what it needs by itself: how many pairs each expert has in earlier chunks
+// and in all.  kFromIds: counted from the routing itself, which makes it the only launch;
+// otherwise from route_count's counts.  Integer LDS atomics: the sums do not depend on order.
+template <bool kFromIds>
+__global__ __launch_bounds__(kChunk) void route_assign_scan_kernel(const int32_t* __restrict__ idx, int64_t T, int k,
+                                                                  int E, int align, const int32_t* __restrict__ counts,
+                                                                  int64_t n_chunks, int32_t* __restrict__ row_map,
+                                                                  int32_t* __restrict__ offsets,
+                                                                  int32_t* __restrict__ src_row) {
+  __shared__ int base[1024], total[1024], offs[1025], wsum[4];
+  __shared__ unsigned long long mask[4][1024];
+  const int tid = threadIdx.x, chunk = blockIdx.x;
+  for (int e = tid; e < E; e += kChunk) {
+    base[e] = total[e] = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) mask[w][e] = 0ull;
+  }
+  __syncthreads();
+  if (kFromIds) {
+    const int n = (int)(T * k), before = chunk * kChunk * k;
+#pragma unroll 4
+    for (int i = tid; i < n; i += kChunk) {
+      const int e = idx[i];
+      if (e < 0 || e >= E) continue;
+      atomicAdd(&total[e], 1);
+      if (i < before) atomicAdd(&base[e], 1);
+    }
+  } else {
+    const int n = (int)n_chunks * E, before = chunk * E;
+#pragma unroll 4
+    for (int i = tid; i < n; i += kChunk) {
+      const int v = counts[i], e = i % E;
+      atomicAdd(&total[e], v);
+      if (i < before) atomicAdd(&base[e], v);
+    }
+  }
+  __syncthreads();
+  int carry = 0;
+  for (int e0 = 0; e0 < E; e0 += kChunk) {  // group offsets, 256 experts at a time
+    const int e = e0 + tid;
+    const int end = carry + chunk_inclusive_sum(e < E ? (total[e] + align - 1) / align * align : 0, wsum);
+    if (e < E) offs[e + 1] = end;
+    if (tid == kChunk - 1) wsum[0] = end;
+    __syncthreads();
+    carry = wsum[0];
+    __syncthreads();
+  }
+  if (tid == 0) offs[0] = 0;
+  __syncthreads();
+  if (chunk == 0)
+    for (int e = tid; e <= E; e += kChunk) offsets[e] = offs[e];
+  // padding rows of the groups (fewer than 128 each): src_row = -1, wave by wave
+  for (int e = chunk * 4 + (tid >> 6); e < E; e += gridDim.x * 4)
+    for (int r = offs[e] + total[e] + (tid & 63); r < offs[e + 1]; r += 64) src_row[r] = -1;
+  for (int e = tid; e < E; e += kChunk) base[e] += offs[e];
+  __syncthreads();
+  assign_rows(idx, chunk, T, k, E, base, mask, row_map, src_row);
+}
+
 // Padding rows of expert e's group (src_row == -1, below offsets[e + 1]): bytes 0x00, scales
-// 2^-126.  A group is padded by fewer than 128 rows, all among its last 128; the workgroup's
-// waves take those rows in turn (wave-uniform tests, one 16-byte store per lane and chunk).
+// 2^-126.  A group is padded by fewer than 128 rows, all among its last 128: those rows' numbers
+// are collected in LDS (two loads for a whole wave, instead of a load before every row, which made
+// a one-wave workgroup take 15 us for a group), then the workgroup's threads share the rows'
+// 16-byte pieces and scales evenly.
 template <typename S>
 __device__ __forceinline__ void pad_group(int e, const int32_t* __restrict__ offsets,
                                           const int32_t* __restrict__ src_row, int64_t H, uint8_t* __restrict__ q,
                                           S* __restrict__ s) {
+  __shared__ int rows[kTile];
+  __shared__ int n_rows;
   const int64_t g0 = offsets[e], g1 = offsets[e + 1];
   const int64_t r0 = g1 - g0 > kTile ? g1 - kTile : g0;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int n_waves = blockDim.x >> 6;
-  const int64_t c16 = H / 16, sh = H / kTile;
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    int n = 0;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int64_t r = r0 + 64 * half + lane;
+      const bool pad = r < g1 && src_row[r] < 0;
+      const unsigned long long m = __ballot(pad);
+      if (pad) rows[n + __popcll(m & (lane == 0 ? 0ull : ~0ull >> (64 - lane)))] = (int)(r - r0);
+      n += __popcll(m);
+    }
+    if (lane == 0) n_rows = n;
+  }
+  __syncthreads();
+  const unsigned n = n_rows, c16 = (unsigned)(H / 16), sh = (unsigned)(H / kTile);
   const u32x4 z = {0u, 0u, 0u, 0u};
-  for (int64_t r = r0 + wave; r < g1; r += n_waves) {
-    if (src_row[r] >= 0) continue;
-    uint8_t* row = q + r * H;
-    for (int64_t c = lane; c < c16; c += 64) stnt16(row + c * 16, z);
-    for (int64_t c = lane; c < sh; c += 64) put_scale(&s[r * sh + c], kTMin);
+  if (c16 >= 64) {  // whole waves per row
+    for (unsigned j = threadIdx.x >> 6; j < n; j += blockDim.x >> 6) {
+      uint8_t* const row = q + (r0 + rows[j]) * H;
+      for (unsigned c = threadIdx.x & 63; c < c16; c += 64) stnt16(row + c * 16, z);
+    }
+  } else {
+    for (unsigned i = threadIdx.x; i < n * c16; i += blockDim.x) {
+      const unsigned j = i / c16;
+      stnt16(q + (r0 + rows[j]) * H + (int64_t)(i - j * c16) * 16, z);
+    }
+  }
+  for (unsigned i = threadIdx.x; i < n * sh; i += blockDim.x) {
+    const unsigned j = i / sh;
+    put_scale(&s[(r0 + rows[j]) * sh + (i - j * sh)], kTMin);
   }
 }
 
 // One workgroup per token: lane c covers 16 elements (two 16-byte loads) of the row, 8
-// lanes one 128-element tile (8-lane DPP amax).  Workgroups T.. T + E - 1 fill the padding
-// rows of expert groups 0..E-1 instead.  The token's k destination rows and
+// lanes one 128-element tile (8-lane DPP amax).  Workgroups 0 .. E - 1 fill the padding rows of
+// the expert groups instead (first, so that they do not trail the tokens').  The token's k destination rows and
 // weights are workgroup-uniform (scalar loads); every copy is one 16-byte store per lane,
 // so a wave writes 1 KB contiguous of one destination row.
 template <bool kWeighted, typename S>
@@ -193,12 +301,12 @@ __global__ __launch_bounds__(kRowThreadsMax) void permute_quant_kernel(const uin
                                                                        const float* __restrict__ row_w, int64_t H,
                                                                        int k, const int32_t* __restrict__ row_map,
                                                                        int64_t M_cap, uint8_t* __restrict__ q,
-                                                                       S* __restrict__ s, int64_t T,
+                                                                       S* __restrict__ s, int E,
                                                                        const int32_t* __restrict__ offsets,
                                                                        const int32_t* __restrict__ src_row) {
-  const int64_t t = blockIdx.x;
-  if (t >= T) {
-    pad_group<S>((int)(t - T), offsets, src_row, H, q, s);
+  const int64_t t = (int64_t)blockIdx.x - E;
+  if (t < 0) {
+    pad_group<S>((int)blockIdx.x, offsets, src_row, H, q, s);
     return;
   }
   const int64_t n16 = H / 16, sh = H / kTile;
@@ -247,12 +355,12 @@ template <typename S>
 __global__ __launch_bounds__(kRowThreadsMax) void permute_quant_dprobs_kernel(
     const uint16_t* __restrict__ dy, const float* __restrict__ row_w, int64_t H, int k,
     const int32_t* __restrict__ row_map, int64_t M_cap, uint8_t* __restrict__ q, S* __restrict__ s,
-    const uint16_t* __restrict__ y_perm, float* __restrict__ dprobs, int64_t T, const int32_t* __restrict__ offsets,
+    const uint16_t* __restrict__ y_perm, float* __restrict__ dprobs, int E, const int32_t* __restrict__ offsets,
     const int32_t* __restrict__ src_row) {
   __shared__ float part[kMaxKDprobs * (kRowThreadsMax / 64)];
-  const int64_t t = blockIdx.x;
-  if (t >= T) {  // padding rows of group t - T (the whole workgroup leaves before any barrier)
-    pad_group<S>((int)(t - T), offsets, src_row, H, q, s);
+  const int64_t t = (int64_t)blockIdx.x - E;
+  if (t < 0) {  // padding rows of a group (the whole workgroup leaves here)
+    pad_group<S>((int)blockIdx.x, offsets, src_row, H, q, s);
     return;
   }
   const int64_t n16 = H / 16, sh = H / kTile;
@@ -376,7 +484,22 @@ hipError_t launch_route(const int32_t* topk_idx, int64_t T, int k, int E, int al
   (void)M_cap;
   const int64_t nc = n_chunks_of(T);
   int32_t* counts = static_cast<int32_t*>(workspace);
+  // Launches of the routing, by what a chunk's workgroup would have to sum by itself (us with the
+  // permute of 128 columns behind them, one / two / three launches): all the pairs, up to 4096 (7
+  // tokens x 6: 10.7 / 12.6 / 13.9; 1024 x 2: 9.2 / 10.5 / 13.1; 1024 x 8: 16.8 / 15.1 / 17.7);
+  // all the counts, up to 8192 (16384 tokens, 64 experts: 25.3 with two launches, 28.8 with three;
+  // 256 experts, 16384 counts: 36.1 / 34.1), and up to 32768 above 512 experts, where the scan's
+  // threads walk their chunks one by one (8192 tokens, 1024 experts: 50.2 / 70.4).
+  const unsigned grid = (unsigned)(nc > 0 ? nc : 1);
+  if (T * k <= 4096) {
+    route_assign_scan_kernel<true><<<grid, kChunk, 0, st>>>(topk_idx, T, k, E, align, nullptr, nc, row_map, offsets, src_row);
+    return hipGetLastError();
+  }
   if (nc > 0) route_count_kernel<<<(unsigned)nc, kChunk, 0, st>>>(topk_idx, T, k, E, counts);
+  if (nc * E <= 8192 || (E > 512 && nc * E <= 32768)) {
+    route_assign_scan_kernel<false><<<grid, kChunk, 0, st>>>(topk_idx, T, k, E, align, counts, nc, row_map, offsets, src_row);
+    return hipGetLastError();
+  }
   route_scan_kernel<<<1, 1024, 0, st>>>(counts, nc, E, align, offsets, src_row);
   if (nc > 0) route_assign_kernel<<<(unsigned)nc, kChunk, 0, st>>>(topk_idx, T, k, E, counts, row_map, src_row);
   return hipGetLastError();
@@ -410,12 +533,12 @@ template <typename S>
 static hipError_t permute_quant_impl(const uint16_t* x, const float* row_w, int64_t T, int64_t H, int k, int E,
                                      const int32_t* row_map, const int32_t* offsets, const int32_t* src_row,
                                      int64_t M_cap, uint8_t* q, S* s, hipStream_t st) {
-  const unsigned grid = (unsigned)(T + E);  // tokens, then one padding workgroup per expert group
+  const unsigned grid = (unsigned)(T + E);  // one padding workgroup per expert group, then the tokens
   if (row_w)
-    permute_quant_kernel<true, S><<<grid, row_threads(H), 0, st>>>(x, row_w, H, k, row_map, M_cap, q, s, T, offsets,
+    permute_quant_kernel<true, S><<<grid, row_threads(H), 0, st>>>(x, row_w, H, k, row_map, M_cap, q, s, E, offsets,
                                                                    src_row);
   else
-    permute_quant_kernel<false, S><<<grid, row_threads(H), 0, st>>>(x, row_w, H, k, row_map, M_cap, q, s, T, offsets,
+    permute_quant_kernel<false, S><<<grid, row_threads(H), 0, st>>>(x, row_w, H, k, row_map, M_cap, q, s, E, offsets,
                                                                     src_row);
   return hipGetLastError();
 }
@@ -437,7 +560,7 @@ static hipError_t permute_quant_dprobs_impl(const uint16_t* dy, const float* row
                                             const int32_t* src_row, int64_t M_cap, uint8_t* q, S* s,
                                             const uint16_t* y_perm, float* dprobs, hipStream_t st) {
   permute_quant_dprobs_kernel<S><<<(unsigned)(T + E), row_threads(H), 0, st>>>(dy, row_w, H, k, row_map, M_cap, q, s,
-                                                                                y_perm, dprobs, T, offsets, src_row);
+                                                                                y_perm, dprobs, E, offsets, src_row);
   return hipGetLastError();
 }
 hipError_t launch_permute_quant_dprobs(const uint16_t* dy, const float* row_w, int64_t T, int64_t H, int k, int E,

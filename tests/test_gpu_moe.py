@@ -715,3 +715,32 @@ def test_token_tile_shapes(case):
                 assert not got[e].any(), e
             else:
                 assert rel_frob(got[e], (1 + accumulate) * want[e]) < GEMM_TOL, e
+
+
+@pytest.mark.parametrize("T,k,E,align", [(1024, 4, 600, 16), (1, 1, 1, 128), (256, 2, 256, 128), (2100, 2, 300, 16),
+                                         (2049, 2, 8, 128), (4200, 1, 1000, 16), (4300, 2, 512, 128)])
+def test_routing_launches(T, k, E, align):
+    """Routing maps where they come from one, two or three launches: the pairs counted by every
+    chunk (up to 4096), the chunks' counts summed by every chunk, and the separate scan; more
+    experts than a workgroup has threads, a last chunk of one token, dropped slots, empty experts."""
+    rng = np.random.default_rng(T + E)
+    idx = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
+    idx[rng.random((T, k)) < 0.05] = -1
+    idx[idx == E // 2] = -1
+    H = 128
+    M_cap = ff8.ff8_rows_bound_aligned(T, k, E, align)
+    row_map, offsets, src_row = (poisoned(s, torch.int32) for s in ((T, k), (E + 1,), (M_cap,)))
+    q, s = poisoned((M_cap, H), torch.uint8), poisoned((M_cap, 1), torch.float32)
+    ws = torch.empty(max(1, ff8.ff8_permute_workspace_bytes(T, k, E)), dtype=torch.uint8, device="cuda")
+    x = workloads.randn_bf16((T, H), 1.0, seed=4)
+    ff8.ff8_permute_quant(dev(x), None, k, E, dev(torch.from_numpy(idx)), False, row_map, offsets, src_row, q, s, ws,
+                          align=align)
+    torch.cuda.synchronize()
+    _, w_off, w_map, w_src = moe.route(idx, E, align)
+    m = int(w_off[-1])
+    assert np.array_equal(host(offsets), w_off)
+    assert np.array_equal(host(row_map), w_map)
+    assert np.array_equal(host(src_row)[:m], w_src) and untouched(src_row[m:])
+    wq, w_s = moe.permute_quant_rows(f64(x), w_src, k)
+    assert np.array_equal(host(q[:m]), wq) and np.array_equal(host(s[:m]), w_s)
+    assert untouched(q[m:]) and untouched(s[m:])
