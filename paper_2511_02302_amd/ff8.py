@@ -118,8 +118,10 @@ def _check(status, name):
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        # the raw handle of the current stream: torch.cuda.current_stream() makes a Stream object
+        # on every call (2.5 us; this 0.1)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _ptr(t, dtype, name, ndim=None):
@@ -127,7 +129,7 @@ def _ptr(t, dtype, name, ndim=None):
         return None
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
-    if t.dtype != dtype:
+    if t.dtype is not dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
@@ -135,12 +137,12 @@ def _ptr(t, dtype, name, ndim=None):
         raise ValueError(f"{name} must be contiguous")
     if ndim is not None and t.dim() != ndim:
         raise ValueError(f"{name} must have {ndim} dimensions, got {t.dim()}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _shape(t, shape, name):
     """t is None or has exactly this shape."""
-    if t is not None and tuple(t.shape) != tuple(shape):
+    if t is not None and t.shape != shape:
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
 
 
@@ -156,11 +158,18 @@ _bf16, _u8, _f32, _i32 = torch.bfloat16, torch.uint8, torch.float32, torch.int32
 def _scale_kind(*scales):
     """Scale storage of a call: float32 tensors (powers of two) or uint8 tensors (UE8M0 bytes,
     T + 127), the same for every scale tensor of the call.  Returns (dtype, C-symbol suffix)."""
+    kind = None
+    for t in scales:
+        if t is not None:
+            if kind is not None and t.dtype is not kind:
+                break
+            kind = t.dtype
+    else:
+        if kind is _f32:
+            return _f32, ""
+        if kind is _u8:
+            return _u8, "_e8m0"
     kinds = {t.dtype for t in scales if t is not None}
-    if kinds == {_f32}:
-        return _f32, ""
-    if kinds == {_u8}:
-        return _u8, "_e8m0"
     raise TypeError(f"scale tensors must all be float32 or all uint8 (UE8M0), got {sorted(map(str, kinds))}")
 
 
@@ -212,7 +221,7 @@ def ff8_permute_quant(x, row_w, k, E, topk_idx, reuse_map, row_map, offsets, src
     args = [_ptr(x, _bf16, "x", 2), _ptr(row_w, _f32, "row_w"), T, H, k, E, _ptr(topk_idx, _i32, "topk_idx"),
             int(reuse_map), _ptr(row_map, _i32, "row_map"), _ptr(offsets, _i32, "offsets"),
             _ptr(src_row, _i32, "src_row"), M_cap, _ptr(q, _u8, "q", 2), _ptr(s, sd, "s", 2),
-            None if workspace is None else ctypes.c_void_p(workspace.data_ptr()), ws]
+            None if workspace is None else workspace.data_ptr(), ws]
     if sfx:
         _check(load().ff8_permute_quant_e8m0(*args, int(align or 128), _stream(stream)), "ff8_permute_quant_e8m0")
     elif align is None:
@@ -282,7 +291,7 @@ def ff8_scaling_aware_transpose_batch(qs, ss, qTs, sTs, offsets=None, E=0, strea
     sd, sfx = _scale_kind(*ss, *sTs)
     if offsets is not None:
         _numel(offsets, E + 1, "offsets")
-    arr = lambda vals: (ctypes.c_void_p * n)(*[v.value for v in vals])
+    arr = lambda vals: (ctypes.c_void_p * n)(*vals)
     q_a = arr([_ptr(q, _u8, f"qs[{i}]", 2) for i, q in enumerate(qs)])
     s_a = arr([_ptr(x, sd, f"ss[{i}]", 2) for i, x in enumerate(ss)])
     qT_a = arr([_ptr(x, _u8, f"qTs[{i}]", 3) for i, x in enumerate(qTs)])
