@@ -31,6 +31,12 @@
 // orientation (256-byte rows) with ds_read_b64_tr_b8, which transposes 8x8 byte
 // blocks across lanes; its rows use the swizzle chunk ^ ((2j ^ j>>2) & 15), j = n%8.
 //
+// fprop / dgrad: a tile with at most 128 rows (what is left of a group after its 256-row tiles; a
+// group just above a multiple of 256 has one of a few rows) runs on half the q panel, 64 rows per
+// wave: half the MFMAs, three quarters of the DMA.  32 experts of about 512 rows, fprop 7168 x 2048
+// 306 -> 278 us, 4096 x 7168 546 -> 499 us, dgrad 561 -> 524 us; 4096 rows each: unchanged (wgrad,
+// whose q is the weight's width, keeps the one form).
+//
 // Grouped scheduling is on the device: tiles are counted per expert from offsets (no
 // host sync).  The kernel is persistent, one workgroup per CU walking its XCD's tiles, so
 // that a tile's epilogue (output staged through one stage buffer, streaming stores)
@@ -49,23 +55,31 @@ constexpr int kBQ = 8;     // q tiles per XCD block
 constexpr int kBP = 4;     // p tiles per XCD block
 static_assert(kBQ * kBP == 32, "an XCD block is the 32 workgroups one XCD runs at once");
 constexpr int kTileBytes = kTP * kBK;  // 32 KB per operand per stage
-#define FF8_STR2(x) #x
-#define FF8_STR(x) FF8_STR2(x)
-constexpr int kReadSlots = 6;          // MFMA slots of a half-step that carry fragment reads
+// Schedule of a stage for tiles with NB 32-row fragments of q per wave (4: 256 q rows; 2: a
+// group's last tile with at most 128 rows, see Tile).  MFMA slots and fragment reads of a
+// half-step, and the tile DMAs of a stage per wave.
+//
 // The stage buffer a stage reads is free once every wave has read its second-half fragments
 // (issued over the first kReadSlots slots of the first half-step): a barrier at slot kEarly
-// publishes that, and the 16 tile DMAs of stage ks+2 into it are spread evenly over the
+// publishes that, and the tile DMAs of stage ks+2 into it are spread evenly over the
 // remaining kDmaSlots MFMA slots of the stage.  (Issued within the second half-step only, the
 // 64 DMA instructions of a workgroup outran the vector-memory path, whose backpressure stalled
 // the in-order waves in front of their next MFMA.)
-constexpr int kEarly = 6;
-constexpr int kDmaSlots = 32 - kEarly;
-static_assert(kEarly >= kReadSlots && kEarly < 16, "the early barrier follows the last fragment read of half 0");
-// tile DMAs issued before DMA slot j (slot j = MFMA slot kEarly + j of half 0, then of half 1)
-__host__ __device__ constexpr int dma_before(int j) { return (16 * j) / kDmaSlots; }
-// DMAs issued in half 0, still in flight at the mid-stage wait (the literal in that wait)
-#define FF8_HALF0_DMAS 6
-static_assert(dma_before(16 - kEarly) == FF8_HALF0_DMAS, "mid-stage vmcnt literal");
+template <int NB>
+struct Sched {
+  static constexpr int kSlots = 4 * NB;  // MFMAs of a half-step
+  static constexpr int kReadSlots = NB == 4 ? 6 : 4;
+  static constexpr int kEarly = NB == 4 ? 6 : 4;
+  static constexpr int kDmas = 8 + 2 * NB;
+  static constexpr int kDmaSlots = 2 * kSlots - kEarly;
+  // tile DMAs issued before DMA slot j (slot j = MFMA slot kEarly + j of half 0, then of half 1)
+  static constexpr int dma_before(int j) { return (kDmas * j) / kDmaSlots; }
+  // DMAs issued in half 0, still in flight at the mid-stage wait
+  static constexpr int kHalf0Dmas = dma_before(kSlots - kEarly);
+  // tile DMA instruction D of the stage (0-7 P, 8-15 Q: with 128 q rows, only the row groups below 16)
+  static constexpr int instr(int d) { return NB == 4 || d < 8 ? d : 8 + ((d - 8) & 1) + 4 * ((d - 8) >> 1); }
+  static_assert(kEarly >= kReadSlots && kEarly < kSlots, "the early barrier follows the last fragment read of half 0");
+};
 // Rotate each XCD block's K order (memory-channel spread).  Measured: +5.6% for fprop,
 // whose two operands are row-major over K; -1% / -3% for dgrad / wgrad, which keep it off.
 template <int MODE> constexpr bool kStaggerK = (MODE == kFprop);
@@ -121,6 +135,7 @@ struct Tile {
   static constexpr bool kSpreadScales = (MODE == kWgrad);
   int wave, lane, wp, wq;
   int nk;
+  bool half;  // at most 128 q rows (a group's last tile): 2 q fragments per wave, Sched<2>
   int k_rot;  // K stages this tile's loop is rotated by (fprop: a multiple of the scale batch)
   int k_lo, k_hi;  // wgrad: valid K bytes [k_lo, 128) of the first stage and [0, k_hi) of the last
   // Stage ks of the loop reads K block (ks + k_rot) mod nk.
@@ -216,26 +231,26 @@ struct Tile {
   }
 
   // Fragment read J of half h of stage buffer B into register set kSetA.
-  //   fprop / wgrad: J 0..15, 16-byte reads: J < 8 -> fq[J/2] half J%2, else fp[(J-8)/2].
-  //   dgrad: J 0..7 as above for fq; J 8..23 -> fp[(J-8)/4], transposing read (J-8)%4.
-  template <int B, int H, bool kSetA, int J>
+  //   fprop / wgrad: 16-byte reads: J < 2 NB -> fq[J/2] half J%2, then 8 of fp.
+  //   dgrad: J < 2 NB as above for fq; then fp, four transposing reads per fragment.
+  template <int NB, int B, int H, bool kSetA, int J>
   __device__ __forceinline__ void read_op() {
     i32x8 (&fp)[4] = kSetA ? fpA : fpB;
     i32x8 (&fq)[4] = kSetA ? fqA : fqB;
     const int l31 = lane & 31, g = lane >> 5;
     const uint8_t* P = stage_buf<B>();
     const uint8_t* Q = stage_buf<B>() + kTileBytes;
-    if constexpr (J < 8) {
-      const int r = 128 * wq + 32 * (J / 2) + l31;
+    if constexpr (J < 2 * NB) {
+      const int r = 32 * NB * wq + 32 * (J / 2) + l31;
       const u32x4 x = *reinterpret_cast<const u32x4*>(Q + r * kBK + (((4 * H + 2 * g + (J % 2)) ^ kswz(r)) << 4));
       fq[J / 2] = with_half(fq[J / 2], x, J % 2);
     } else if constexpr (MODE != kDgrad) {
-      const int a = (J - 8) / 2, half = (J - 8) % 2;
+      const int a = (J - 2 * NB) / 2, half = (J - 2 * NB) % 2;
       const int r = 128 * wp + 32 * a + l31;
       const u32x4 x = *reinterpret_cast<const u32x4*>(P + r * kBK + (((4 * H + 2 * g + half) ^ kswz(r)) << 4));
       fp[a] = with_half(fp[a], x, half);
     } else {
-      const int a = (J - 8) / 4, rr = (J - 8) % 4;
+      const int a = (J - 2 * NB) / 4, rr = (J - 2 * NB) % 4;
       const int gg = lane >> 4, hh = lane & 1, ii = (lane & 15) >> 1;
       const int kl = 128 * wp + 32 * a + 16 * (gg & 1) + 8 * hh;
       const int n = 64 * H + 32 * (gg >> 1) + 8 * rr + ii;
@@ -246,19 +261,20 @@ struct Tile {
       fp[a][2 * rr + 1] = t[1];
     }
   }
-  static constexpr int kFragReads = (MODE == kDgrad) ? 24 : 16;
-  template <int B, int H, bool kSetA, int J>
+  template <int NB>
+  static constexpr int kFragReads = 2 * NB + ((MODE == kDgrad) ? 16 : 8);
+  template <int NB, int B, int H, bool kSetA, int J>
   __device__ __forceinline__ void read_all_from() {
-    if constexpr (J < kFragReads) {
-      read_op<B, H, kSetA, J>();
-      read_all_from<B, H, kSetA, J + 1>();
+    if constexpr (J < kFragReads<NB>) {
+      read_op<NB, B, H, kSetA, J>();
+      read_all_from<NB, B, H, kSetA, J + 1>();
     }
   }
   // Scales of batch b (LDS buffer b % 2): read the four K-block scales of each row of one
   // operand this lane multiplies into raw[R] (kQ, or wgrad P: rows 128 w + 32 R + l for
   // R = 0..3; fprop / dgrad P: the wave's one weight-block row, raw[0] only) ...
   // Rows R0..R1-1 only (read and packed a few at a time, to keep few raw rows live).
-  template <bool kQ, int R0, int R1>
+  template <int NB, bool kQ, int R0, int R1>
   __device__ __forceinline__ void read_scale_rows(int b, u32x4 (&raw)[4]) {
     const u32x4* S = reinterpret_cast<const u32x4*>(&g_sc[b & 1][0]);
     const int l31 = opaque_lane() & 31;  // recomputed here rather than held through the tile
@@ -267,25 +283,25 @@ struct Tile {
     } else if constexpr (kE8) {
       const uint8_t* B8 = reinterpret_cast<const uint8_t*>(&g_sc[b & 1][kQ ? kTP * kScaleBatch : 0]);
       if constexpr (MODE == kWgrad) {  // [K block][256 row bytes]
-        const int row = (kQ ? 128 * wq : 128 * wp) + l31;
+        const int row = (kQ ? 32 * NB * wq : 128 * wp) + l31;
 #pragma unroll
         for (int R = R0; R < R1; ++R)
 #pragma unroll
           for (int j = 0; j < kScaleBatch; ++j) raw[R][j] = B8[j * kTP + row + 32 * R];
       } else {  // Q rows: one dword of four K-block bytes each
 #pragma unroll
-        for (int R = R0; R < R1; ++R) raw[R][0] = reinterpret_cast<const uint32_t*>(B8)[128 * wq + 32 * R + l31];
+        for (int R = R0; R < R1; ++R) raw[R][0] = reinterpret_cast<const uint32_t*>(B8)[32 * NB * wq + 32 * R + l31];
       }
     } else if constexpr (MODE == kWgrad) {  // [K block][256 rows]
       const float* F = &g_sc[b & 1][kQ ? kTP * kScaleBatch : 0];
-      const int row = (kQ ? 128 * wq : 128 * wp) + l31;
+      const int row = (kQ ? 32 * NB * wq : 128 * wp) + l31;
 #pragma unroll
       for (int R = R0; R < R1; ++R)
 #pragma unroll
         for (int j = 0; j < kScaleBatch; ++j) raw[R][j] = __float_as_uint(F[j * kTP + row + 32 * R]);
     } else {  // Q rows of four K-block floats
 #pragma unroll
-      for (int R = R0; R < R1; ++R) raw[R] = S[kTP + 128 * wq + 32 * R + l31];
+      for (int R = R0; R < R1; ++R) raw[R] = S[kTP + 32 * NB * wq + 32 * R + l31];
     }
   }
   // ... and pack them: word j holds the E8M0 byte (the fp32 exponent field of a
@@ -326,61 +342,63 @@ struct Tile {
     }
   }
 
-  template <bool kSetA, int S4, int I>
+  template <int NB, bool kSetA, int S4, int I>
   __device__ __forceinline__ void mfma_op() {
     i32x8 (&fp)[4] = kSetA ? fpA : fpB;
     i32x8 (&fq)[4] = kSetA ? fqA : fqB;
-    constexpr int A = I / 4, Bq = I % 4;
+    constexpr int A = I / NB, Bq = I % NB;
     acc[A][Bq] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp[A], fq[Bq], acc[A][Bq], 0, 0, A, (int)cp[S4], Bq,
                                                                    (int)cq[S4]);
   }
   // Tile DMA instructions D0..D1-1 of stage ks_dma into buffer B.
-  template <int B, int D0, int D1>
+  template <int NB, int B, int D0, int D1>
   __device__ __forceinline__ void dma_range(int ks_dma) {
     if constexpr (D0 < D1) {
-      dma_tile<B, D0, false, true>(ks_dma);
-      dma_range<B, D0 + 1, D1>(ks_dma);
+      dma_tile<B, Sched<NB>::instr(D0), false, true>(ks_dma);
+      dma_range<NB, B, D0 + 1, D1>(ks_dma);
     }
   }
   // DMA slot J (0..kDmaSlots-1) of a stage: its share of the tile DMAs of stage ks_dma, and, in
   // the second half-step of the first stage of a scale batch, the next batch's scale DMAs
-  // (slot indices of half 1 are 16 - kEarly + I).
-  template <int B, int S4, int J>
+  // (slot indices of half 1 are kSlots - kEarly + I).
+  template <int NB, int B, int S4, int J>
   __device__ __forceinline__ void dma_slot(int ks_dma, int ks_next) {
-    dma_range<B, dma_before(J), dma_before(J + 1)>(ks_dma);
-    if constexpr (S4 == 0 && J == 16 - kEarly + 1) dma_scale_p<true>((ks_next >> 2) + 1);
-    if constexpr (S4 == 0 && J == 16 - kEarly + 3) dma_scale_q<true>((ks_next >> 2) + 1);
+    using Sc = Sched<NB>;
+    dma_range<NB, B, Sc::dma_before(J), Sc::dma_before(J + 1)>(ks_dma);
+    if constexpr (S4 == 0 && J == Sc::kSlots - Sc::kEarly + 1) dma_scale_p<true>((ks_next >> 2) + 1);
+    if constexpr (S4 == 0 && J == Sc::kSlots - Sc::kEarly + 3) dma_scale_q<true>((ks_next >> 2) + 1);
   }
   // Fragment reads of MFMA slot I: the half-step's kFragReads reads spread evenly over
   // its first kReadSlots slots.
-  template <int B, int H, bool kSetA, int J, int JEnd>
+  template <int NB, int B, int H, bool kSetA, int J, int JEnd>
   __device__ __forceinline__ void reads_range() {
     if constexpr (J < JEnd) {
-      read_op<B, H, kSetA, J>();
-      reads_range<B, H, kSetA, J + 1, JEnd>();
+      read_op<NB, B, H, kSetA, J>();
+      reads_range<NB, B, H, kSetA, J + 1, JEnd>();
     }
   }
-  template <int B, int H, bool kSetA, int I>
+  template <int NB, int B, int H, bool kSetA, int I>
   __device__ __forceinline__ void reads_of_slot() {
-    if constexpr (I < kReadSlots)
-      reads_range<B, H, kSetA, I * kFragReads / kReadSlots, (I + 1) * kFragReads / kReadSlots>();
+    constexpr int n = kFragReads<NB>, slots = Sched<NB>::kReadSlots;
+    if constexpr (I < slots) reads_range<NB, B, H, kSetA, I * n / slots, (I + 1) * n / slots>();
   }
 
   // First half-step of stage ks (buffer B): MFMAs on set A; the reads of the second half (same
   // buffer) into set B go out over the first kReadSlots MFMAs; at slot kEarly every wave has
   // them (lgkmcnt) and a barrier frees buffer B, into which the DMA of stage ks+2 starts.
-  template <int B, int S4, int I>
+  template <int NB, int B, int S4, int I>
   __device__ __forceinline__ void half0_from(int ks_dma, int ks_next) {
-    if constexpr (I < 16) {
-      mfma_op<true, S4, I>();
-      reads_of_slot<B, 1, false, I>();
-      if constexpr (I == kEarly) {
+    using Sc = Sched<NB>;
+    if constexpr (I < Sc::kSlots) {
+      mfma_op<NB, true, S4, I>();
+      reads_of_slot<NB, B, 1, false, I>();
+      if constexpr (I == Sc::kEarly) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
       }
-      if constexpr (I >= kEarly) dma_slot<B, S4, I - kEarly>(ks_dma, ks_next);
+      if constexpr (I >= Sc::kEarly) dma_slot<NB, B, S4, I - Sc::kEarly>(ks_dma, ks_next);
       __builtin_amdgcn_sched_barrier(0);
-      half0_from<B, S4, I + 1>(ks_dma, ks_next);
+      half0_from<NB, B, S4, I + 1>(ks_dma, ks_next);
     }
   }
   // Second half-step: MFMAs on set B.  The rest of stage ks+2's DMA (with the next scale
@@ -388,49 +406,59 @@ struct Tile {
   // stage ks+1's first half (other buffer) into set A over the first kReadSlots MFMAs; in
   // the last stage of a batch the next batch's scales are read and packed (wgrad: those of P
   // in the second stage, kSpreadScales).
-  template <int B, int S4, int I>
+  template <int NB, int B, int S4, int I>
   __device__ __forceinline__ void half1_from(int ks_dma, int ks_next) {
-    if constexpr (I < 16) {
-      mfma_op<false, S4, I>();
-      dma_slot<B, S4, 16 - kEarly + I>(ks_dma, ks_next);
-      reads_of_slot<1 - B, 0, true, I>();
-      if constexpr (kSpreadScales) {
-        if constexpr (S4 == 1 && I == 8) read_scale_rows<false, 0, 2>((ks_next >> 2) + 1, rsp);
+    using Sc = Sched<NB>;
+    if constexpr (I < Sc::kSlots) {
+      mfma_op<NB, false, S4, I>();
+      dma_slot<NB, B, S4, Sc::kSlots - Sc::kEarly + I>(ks_dma, ks_next);
+      reads_of_slot<NB, 1 - B, 0, true, I>();
+      if constexpr (NB == 2) {  // half the slots: two rows of P at a time, both of Q's
+        constexpr bool p_here = S4 == (kSpreadScales ? 1 : 3), q_here = S4 == 3;
+        const int bp = kSpreadScales ? (ks_next >> 2) + 1 : ks_next >> 2;
+        if constexpr (p_here && I == 4) read_scale_rows<NB, false, 0, 2>(bp, rsp);
+        if constexpr (p_here && I == 5) pack_scales<false, 0, 2>(rsp, np);
+        if constexpr (p_here && I == 5) read_scale_rows<NB, false, 2, 4>(bp, rsp);
+        if constexpr (p_here && I == 6) pack_scales<false, 2, 4>(rsp, np);
+        if constexpr (q_here && I == 6) read_scale_rows<NB, true, 0, 2>(ks_next >> 2, rsq);
+        if constexpr (q_here && I == 7) pack_scales<true, 0, 2>(rsq, nq);
+      } else if constexpr (kSpreadScales) {
+        if constexpr (S4 == 1 && I == 8) read_scale_rows<NB, false, 0, 2>((ks_next >> 2) + 1, rsp);
         if constexpr (S4 == 1 && I == 10) pack_scales<false, 0, 2>(rsp, np);
-        if constexpr (S4 == 1 && I == 12) read_scale_rows<false, 2, 4>((ks_next >> 2) + 1, rsp);
+        if constexpr (S4 == 1 && I == 12) read_scale_rows<NB, false, 2, 4>((ks_next >> 2) + 1, rsp);
         if constexpr (S4 == 1 && I == 14) pack_scales<false, 2, 4>(rsp, np);
-        if constexpr (S4 == 3 && I == 8) read_scale_rows<true, 0, 2>(ks_next >> 2, rsq);
+        if constexpr (S4 == 3 && I == 8) read_scale_rows<NB, true, 0, 2>(ks_next >> 2, rsq);
         if constexpr (S4 == 3 && I == 10) pack_scales<true, 0, 2>(rsq, nq);
-        if constexpr (S4 == 3 && I == 12) read_scale_rows<true, 2, 4>(ks_next >> 2, rsq);
+        if constexpr (S4 == 3 && I == 12) read_scale_rows<NB, true, 2, 4>(ks_next >> 2, rsq);
         if constexpr (S4 == 3 && I == 14) pack_scales<true, 2, 4>(rsq, nq);
       } else {
-        if constexpr (S4 == 3 && I == 8) read_scale_rows<false, 0, 2>(ks_next >> 2, rsp);
-        if constexpr (S4 == 3 && I == 9) read_scale_rows<true, 0, 2>(ks_next >> 2, rsq);
+        if constexpr (S4 == 3 && I == 8) read_scale_rows<NB, false, 0, 2>(ks_next >> 2, rsp);
+        if constexpr (S4 == 3 && I == 9) read_scale_rows<NB, true, 0, 2>(ks_next >> 2, rsq);
         if constexpr (S4 == 3 && I == 10) pack_scales<false, 0, 2>(rsp, np);
-        if constexpr (S4 == 3 && I == 11) read_scale_rows<false, 2, 4>(ks_next >> 2, rsp);
+        if constexpr (S4 == 3 && I == 11) read_scale_rows<NB, false, 2, 4>(ks_next >> 2, rsp);
         if constexpr (S4 == 3 && I == 11) pack_scales<true, 0, 2>(rsq, nq);
-        if constexpr (S4 == 3 && I == 12) read_scale_rows<true, 2, 4>(ks_next >> 2, rsq);
+        if constexpr (S4 == 3 && I == 12) read_scale_rows<NB, true, 2, 4>(ks_next >> 2, rsq);
         if constexpr (S4 == 3 && I == 13) pack_scales<false, 2, 4>(rsp, np);
         if constexpr (S4 == 3 && I == 14) pack_scales<true, 2, 4>(rsq, nq);
       }
       __builtin_amdgcn_sched_barrier(0);
-      half1_from<B, S4, I + 1>(ks_dma, ks_next);
+      half1_from<NB, B, S4, I + 1>(ks_dma, ks_next);
     }
   }
 
   // Stage ks, S4 = ks % 4 (buffer S4 % 2).  Between the halves, wait for this wave's DMA of
   // stage ks+1 (and older: the scale batch) -- loads complete in order, so all but the
-  // FF8_HALF0_DMAS just issued for stage ks+2 -- then barrier: stage ks+1 is visible to all.
+  // kHalf0Dmas just issued for stage ks+2 -- then barrier: stage ks+1 is visible to all.
   // Stages past the end are reloads of the last one (in bounds, never multiplied).
-  template <int S4>
+  template <int NB, int S4>
   __device__ __forceinline__ void stage(int ks) {
     constexpr int B = S4 % 2;
     const int ks_dma = ks + 2 < nk ? ks + 2 : nk - 1;
-    half0_from<B, S4, 0>(ks_dma, ks + 1);
-    asm volatile("s_waitcnt vmcnt(" FF8_STR(FF8_HALF0_DMAS) ") lgkmcnt(0)" ::: "memory");
+    half0_from<NB, B, S4, 0>(ks_dma, ks + 1);
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(Sched<NB>::kHalf0Dmas) : "memory");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    half1_from<B, S4, 0>(ks_dma, ks + 1);
+    half1_from<NB, B, S4, 0>(ks_dma, ks + 1);
     if constexpr (S4 == 3) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -511,6 +539,7 @@ __device__ __forceinline__ void setup_tile(Tile<MODE, SC>& T, const GemmArgs& g,
   const uint32_t q0 = (uint32_t)t.q0, k0 = (uint32_t)t.k0, p0 = (uint32_t)t.p0;
   const uint32_t Np = (uint32_t)g.Np, Kdim = (uint32_t)g.Kdim, M_cap = (uint32_t)g.M_cap;
   T.nk = t.nk;
+  T.half = MODE != kWgrad && t.q_end - t.q0 <= 128;
   T.k_lo = t.k_lo;
   T.k_hi = t.k_hi;
   const uint32_t q_ld = (MODE == kWgrad) ? M_cap : Kdim;
@@ -616,7 +645,7 @@ __device__ __forceinline__ void setup_tile(Tile<MODE, SC>& T, const GemmArgs& g,
 // The stores are non-temporal: the output is not re-read here, and streaming it keeps the
 // operand panels that the XCD's other workgroups are still reading in L2.  A wave only
 // rewrites its own region, after its own reads (LDS order), so passes need no barrier.
-template <int MODE, typename SC>
+template <int NB, int MODE, typename SC>
 __device__ __forceinline__ void epilogue(Tile<MODE, SC>& T, const GemmArgs& g, const TileInfo& t) {
   const int lane = opaque_lane(), wave = T.wave, wp = T.wp, wq = T.wq;
   lds_u8* const region = (lds_u8*)g_st1 + wave * 16384;
@@ -625,9 +654,9 @@ __device__ __forceinline__ void epilogue(Tile<MODE, SC>& T, const GemmArgs& g, c
   if (MODE == kWgrad) {
     // uniform base of this wave's 128 x 128 sub-tile, 32-bit lane offsets from it
     uint8_t* const dw = reinterpret_cast<uint8_t*>(
-        static_cast<float*>(g.out) + ((size_t)t.e * g.Nq + t.q0 + 128 * wq) * g.Np + t.p0 + 128 * wp);
+        static_cast<float*>(g.out) + ((size_t)t.e * g.Nq + t.q0 + 32 * NB * wq) * g.Np + t.p0 + 128 * wp);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
+    for (int b = 0; b < NB; ++b) {
       // rows ql = l31 of 512 bytes (q = 32 b + ql); chunk c = p / 4 = 8a + 2gr + h
 #pragma unroll
       for (int a = 0; a < 4; ++a)
@@ -650,7 +679,7 @@ __device__ __forceinline__ void epilogue(Tile<MODE, SC>& T, const GemmArgs& g, c
 #pragma unroll
       for (int it = 0; it < 16; ++it) {
         const int qr = 32 * b + 2 * it + h;  // row within the wave's sub-tile
-        if (!p_ok || t.q0 + 128 * wq + qr >= t.q_end) continue;
+        if (!p_ok || t.q0 + 32 * NB * wq + qr >= t.q_end) continue;
         uint8_t* dst = dw + (uint32_t)(qr * g.Np + 4 * l31) * 4u;
         if (g.accumulate) {
           const u32x4 old = ld16(dst);
@@ -665,10 +694,10 @@ __device__ __forceinline__ void epilogue(Tile<MODE, SC>& T, const GemmArgs& g, c
     }
   } else {
     // uniform base of this wave's 128 x 128 sub-tile, 32-bit lane offsets from it
-    uint8_t* const out = reinterpret_cast<uint8_t*>(static_cast<uint16_t*>(g.out) + (size_t)(t.q0 + 128 * wq) * g.Np +
+    uint8_t* const out = reinterpret_cast<uint8_t*>(static_cast<uint16_t*>(g.out) + (size_t)(t.q0 + 32 * NB * wq) * g.Np +
                                                     t.p0 + 128 * wp);
 #pragma unroll
-    for (int ph = 0; ph < 2; ++ph) {
+    for (int ph = 0; ph < NB / 2; ++ph) {
       // rows ql = 32bb + l31 of 256 bytes (q = 64 ph + ql); 8-byte piece (p = 32a + 8gr + 4h)
       // in chunk 4a + gr, half h
 #pragma unroll
@@ -695,37 +724,53 @@ __device__ __forceinline__ void epilogue(Tile<MODE, SC>& T, const GemmArgs& g, c
 #pragma unroll
       for (int it = 0; it < 16; ++it) {
         const int qr = 64 * ph + 4 * it + (lane >> 4);  // row within the wave's sub-tile
-        if (!p_ok || t.q0 + 128 * wq + qr >= t.q_end) continue;
+        if (!p_ok || t.q0 + 32 * NB * wq + qr >= t.q_end) continue;
         stnt16(out + (uint32_t)(qr * g.Np + 8 * c) * 2u, v[it]);
       }
     }
   }
 }
 
+// Tile DMA of a stage outside the K loop into buffer B (instructions D..kDmas-1).
+template <int NB, int B, int MODE, typename SC, int D = 0>
+__device__ __forceinline__ void dma_stage(Tile<MODE, SC>& T, int ks) {
+  if constexpr (D < Sched<NB>::kDmas) {
+    T.template dma_tile<B, Sched<NB>::instr(D), MODE == kWgrad>(ks);
+    dma_stage<NB, B, MODE, SC, D + 1>(T, ks);
+  }
+}
 // First-stage DMA of a tile: stage 0 into buffer 0, then the scale batch 0 (buffer 0).
 template <int MODE, typename SC>
 __device__ __forceinline__ void dma_first_stage(Tile<MODE, SC>& T) {
-  T.template dma_tile<0, 0, MODE == kWgrad>(0); T.template dma_tile<0, 1, MODE == kWgrad>(0); T.template dma_tile<0, 2, MODE == kWgrad>(0);
-  T.template dma_tile<0, 3, MODE == kWgrad>(0); T.template dma_tile<0, 4, MODE == kWgrad>(0); T.template dma_tile<0, 5, MODE == kWgrad>(0);
-  T.template dma_tile<0, 6, MODE == kWgrad>(0); T.template dma_tile<0, 7, MODE == kWgrad>(0); T.template dma_tile<0, 8, MODE == kWgrad>(0);
-  T.template dma_tile<0, 9, MODE == kWgrad>(0); T.template dma_tile<0, 10, MODE == kWgrad>(0); T.template dma_tile<0, 11, MODE == kWgrad>(0);
-  T.template dma_tile<0, 12, MODE == kWgrad>(0); T.template dma_tile<0, 13, MODE == kWgrad>(0); T.template dma_tile<0, 14, MODE == kWgrad>(0);
-  T.template dma_tile<0, 15, MODE == kWgrad>(0);
+  if (MODE != kWgrad && T.half) dma_stage<2, 0>(T, 0); else dma_stage<4, 0>(T, 0);
   T.template dma_scale_p<false>(0);
   T.template dma_scale_q<false>(0);
 }
-// Second-stage DMA (stage 1, or a reload of stage 0 when nk == 1) into buffer 1: exactly
-// kStage1Dma instructions per wave, the newest in flight when stage 0 is awaited.
-constexpr int kStage1Dma = 16;
-template <int MODE, typename SC>
-__device__ __forceinline__ void dma_second_stage(Tile<MODE, SC>& T) {
-  const int s1 = T.nk > 1 ? 1 : 0;
-  T.template dma_tile<1, 0, MODE == kWgrad>(s1); T.template dma_tile<1, 1, MODE == kWgrad>(s1); T.template dma_tile<1, 2, MODE == kWgrad>(s1);
-  T.template dma_tile<1, 3, MODE == kWgrad>(s1); T.template dma_tile<1, 4, MODE == kWgrad>(s1); T.template dma_tile<1, 5, MODE == kWgrad>(s1);
-  T.template dma_tile<1, 6, MODE == kWgrad>(s1); T.template dma_tile<1, 7, MODE == kWgrad>(s1); T.template dma_tile<1, 8, MODE == kWgrad>(s1);
-  T.template dma_tile<1, 9, MODE == kWgrad>(s1); T.template dma_tile<1, 10, MODE == kWgrad>(s1); T.template dma_tile<1, 11, MODE == kWgrad>(s1);
-  T.template dma_tile<1, 12, MODE == kWgrad>(s1); T.template dma_tile<1, 13, MODE == kWgrad>(s1); T.template dma_tile<1, 14, MODE == kWgrad>(s1);
-  T.template dma_tile<1, 15, MODE == kWgrad>(s1);
+// K loop of a tile whose first stage is in flight.
+template <int NB, int MODE, typename SC>
+__device__ __forceinline__ void k_loop(Tile<MODE, SC>& T) {
+  const int nk = T.nk;
+  if (MODE != kWgrad) T.lane = opaque_lane();  // LDS addresses are made here, not kept for both loops across tiles
+  // stage 1 (or a reload of stage 0 when nk == 1) into buffer 1
+  dma_stage<NB, 1>(T, nk > 1 ? 1 : 0);
+  // stage 0 and scale batch 0 have landed when at most the stage-1 DMAs are in flight
+  // (loads retire in order; older epilogue stores still in flight only make this wait longer)
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(Sched<NB>::kDmas) : "memory");
+  T.template read_all_from<NB, 0, 0, true, 0>();
+  {
+    u32x4 raw[4];
+    T.template read_scale_rows<NB, false, 0, 4>(0, raw);
+    T.template pack_scales<false, 0, 4>(raw, T.cp);
+    T.template read_scale_rows<NB, true, 0, NB>(0, raw);
+    T.template pack_scales<true, 0, NB>(raw, T.cq);
+  }
+  for (int ks = 0; ks < nk; ks += 4) {
+    T.template stage<NB, 0>(ks);
+    if (ks + 1 < nk) T.template stage<NB, 1>(ks + 1);
+    if (ks + 2 < nk) T.template stage<NB, 2>(ks + 2);
+    if (ks + 3 < nk) T.template stage<NB, 3>(ks + 3);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the tail's reload DMAs have landed
 }
 
 // Semi-persistent: the grid is a sequence of groups of S workgroups per XCD (S = 32 on
@@ -870,28 +915,9 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
       for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) T.acc[a][b][v] = 0.0f;
-    const int nk = T.nk;
-    if (nk > 0) {
-      dma_second_stage<MODE, SC>(T);
-      // stage 0 and scale batch 0 have landed when at most the stage-1 DMAs are in flight
-      // (loads retire in order; older epilogue stores still in flight only make this wait longer)
-      asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");
-      static_assert(kStage1Dma == 16, "the wait count above is the stage-1 DMA count");
-      T.template read_all_from<0, 0, true, 0>();
-      {
-        u32x4 raw[4];
-        T.template read_scale_rows<false, 0, 4>(0, raw);
-        T.template pack_scales<false, 0, 4>(raw, T.cp);
-        T.template read_scale_rows<true, 0, 4>(0, raw);
-        T.template pack_scales<true, 0, 4>(raw, T.cq);
-      }
-      for (int ks = 0; ks < nk; ks += 4) {
-        T.template stage<0>(ks);
-        if (ks + 1 < nk) T.template stage<1>(ks + 1);
-        if (ks + 2 < nk) T.template stage<2>(ks + 2);
-        if (ks + 3 < nk) T.template stage<3>(ks + 3);
-      }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the tail's reload DMAs have landed
+    const bool half = MODE != kWgrad && T.half;
+    if (T.nk > 0) {
+      if (half) k_loop<2>(T); else k_loop<4>(T);
     }
     lds_barrier();  // every wave is done with the stage buffers and the scale batches
     TileInfo tn;
@@ -901,7 +927,9 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
       setup_tile<MODE, SC>(T, g, tn);
       if (T.nk > 0) dma_first_stage<MODE, SC>(T);  // buffer 0 and scale batch 0, under the epilogue
     }
-    if (!(MODE == kWgrad && t.nk == 0 && g.accumulate)) epilogue<MODE, SC>(T, g, t);
+    if (!(MODE == kWgrad && t.nk == 0 && g.accumulate)) {
+      if (half) epilogue<2>(T, g, t); else epilogue<4>(T, g, t);
+    }
     if (!more) break;
     t = tn;
     lds_barrier();  // buffer 1 is free for the next tile's second stage

@@ -139,3 +139,36 @@ def test_layer_step_e8m0_equals_f32(case):
     for n in ("xs", "hs", "dys", "das") + (("as",) if ckpt else ()):
         assert np.array_equal(host(b8[n][:m_pad]), _bytes(b[n][:m_pad])), n
     assert L8.saved_activation_bytes() < L.saved_activation_bytes()
+
+
+# Row groups that reach every tile shape of the row-wise products (64-, 128- and 256-row tiles, and
+# the 128-row last tile of a group among 256-row tiles), and token groups for wgrad's two.
+@pytest.mark.parametrize("mode,rows,cols,depth", [
+    *[(m, *c) for m in ("fprop", "dgrad") for c in (([16, 64, 0, 48], 1024, 512),
+                                                    ([128, 80, 16, 112, 0, 128, 96, 80], 512, 1536),
+                                                    ([512, 272], 1024, 1024), ([1024, 784], 22528, 512))],
+    ("wgrad", [16, 128, 0, 48], 512, 1152), ("wgrad", [640, 16, 528, 0], 1920, 1024),
+    ("wgrad", [1024, 912, 1040, 1024], 2048, 4096)])
+def test_tile_shapes_e8m0_equal_f32(mode, rows, cols, depth):
+    """The same bytes and bits from float32 scales and from their UE8M0 bytes."""
+    E, rng = len(rows), np.random.default_rng(sum(rows) + cols)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    M_cap = -(-(int(off[-1]) + 16) // 128) * 128
+    code = lambda *shape: torch.from_numpy(rng.choice(np.r_[0:127, 128:255].astype(np.uint8), size=shape)).cuda()
+    exps = lambda *shape: torch.from_numpy(rng.integers(121, 130, size=shape).astype(np.uint8)).cuda()
+    f32 = lambda e: (e.to(torch.int32) << 23).view(torch.float32)
+    offsets = torch.from_numpy(off).cuda()
+    if mode == "wgrad":
+        ops = [code(M_cap // 128, cols, 128), exps(M_cap // 128, cols), code(M_cap // 128, depth, 128),
+               exps(M_cap // 128, depth)]
+        out = [torch.empty((E, cols, depth), dtype=torch.float32, device="cuda") for _ in range(2)]
+    else:
+        N, K = (cols, depth) if mode == "fprop" else (depth, cols)
+        ops = [code(M_cap, depth), exps(M_cap, depth // 128), code(E, N, K), exps(E, N // 128, K // 128)]
+        out = [torch.zeros((M_cap, cols), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    call = getattr(ff8, f"ff8_grouped_gemm_{mode}")
+    call(ops[0], f32(ops[1]), ops[2], f32(ops[3]), offsets, out[0])
+    call(*ops, offsets, out[1])
+    torch.cuda.synchronize()
+    assert torch.equal(out[0].view(torch.uint8), out[1].view(torch.uint8))
+    assert bool(out[0].any())
