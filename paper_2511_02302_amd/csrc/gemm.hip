@@ -53,7 +53,8 @@ constexpr int kTP = 256;   // p tile
 constexpr int kTQ = 256;   // q tile
 constexpr int kBQ = 8;     // q tiles per XCD block
 constexpr int kBP = 4;     // p tiles per XCD block
-static_assert(kBQ * kBP == 32, "an XCD block is the 32 workgroups one XCD runs at once");
+constexpr int kPersistSlots = kBQ * kBP;  // workgroups per XCD and group
+static_assert(kPersistSlots == 32, "an XCD block is the 32 workgroups one XCD runs at once");
 constexpr int kTileBytes = kTP * kBK;  // 32 KB per operand per stage
 // Schedule of a stage for tiles with NB 32-row fragments of q per wave (4: 256 q rows; 2: a
 // group's last tile with at most 128 rows, see Tile).  MFMA slots and fragment reads of a
@@ -492,14 +493,32 @@ __device__ __forceinline__ void wgrad_k_range(const GemmArgs& g, int e, TileInfo
 
 // Tile w_in of XCD block blk (kBQ x kBP tiles, p fastest).  False for tiles past the
 // edges.  fprop/dgrad: q tiles are 256-row tiles of the expert groups (g_cum / g_off:
-// cumulative tile counts and row offsets per expert, in LDS).
-template <int MODE>
-__device__ __forceinline__ bool decode_tile(const GemmArgs& g, int blk, int w_in, TileInfo& t) {
-  const int n_pb = (g.n_pt + kBP - 1) / kBP;
-  const int qb = blk / n_pb, pb = blk - qb * n_pb;
-  const int qg = qb * kBQ + w_in / kBP;  // global q-tile index
-  const int pt = pb * kBP + w_in % kBP;
-  if (pt >= g.n_pt) return false;
+// cumulative tile counts and row offsets per expert, in LDS); n_qg: q tiles of the launch.
+// kPack (p tiles not a multiple of kBP): every third or so block would be cut by the p edge and
+// leave its XCD a part of the work, so the blocks' tiles are packed into chunks of 32 in block
+// order, and blk is a chunk; every chunk but the last is full.  64 experts of 1024 rows, 2048 x
+// 1408 (6 p tiles): dgrad 254 -> 220 us, wgrad 364 -> 310.  With whole blocks only, the longer
+// lookup between two tiles costs 1-2%, so those keep the short one.
+template <int MODE, bool kPack>
+__device__ __forceinline__ bool decode_tile(const GemmArgs& g, int n_qg, int blk, int w_in, TileInfo& t) {
+  int qg, pt;  // global q-tile index, p tile
+  if constexpr (kPack) {
+    const int l = blk * kPersistSlots + w_in;
+    if (l >= n_qg * g.n_pt) return false;
+    const int row = l / (kBQ * g.n_pt), l_q = l - row * kBQ * g.n_pt;  // row of blocks
+    const int nq = min(kBQ, n_qg - row * kBQ);
+    const int pb = l_q / (kBP * nq), l_p = l_q - pb * kBP * nq;
+    const int np = min(kBP, g.n_pt - pb * kBP);
+    const int lq = l_p / np;
+    qg = row * kBQ + lq;
+    pt = pb * kBP + l_p - lq * np;
+  } else {
+    const int n_pb = (g.n_pt + kBP - 1) / kBP;
+    const int qb = blk / n_pb, pb = blk - qb * n_pb;
+    qg = qb * kBQ + w_in / kBP;
+    pt = pb * kBP + w_in % kBP;
+    if (pt >= g.n_pt) return false;
+  }
   t.blk = blk;
   t.p0 = (int64_t)pt * kTP;
   if (MODE != kWgrad) {
@@ -795,7 +814,6 @@ __device__ __forceinline__ void k_loop(Tile<MODE, SC>& T) {
 // stage follows once the epilogue has left buffer 1.  All control flow is
 // workgroup-uniform (tile decode from uniform values), so every barrier is reached by all
 // four waves, and every wave leaves the tile loop with the same tile count.
-constexpr int kPersistSlots = kBQ * kBP;  // workgroups per XCD and group
 constexpr int kRoundsPerWg = 4;           // work rounds (tiles) per workgroup
 
 // Workgroup barrier that waits for this wave's LDS accesses only: global stores may stay in
@@ -821,10 +839,18 @@ __device__ __forceinline__ void decode_share_tile(const GemmArgs& g, int xcd, in
 }
 
 // Next tile of this workgroup from round k on, below round k_end (k advances past empty
-// edge tiles).
-template <int MODE>
-__device__ __forceinline__ bool next_tile(const GemmArgs& g, int xcd, int slot, int n_slots, int n_blocks, int k_end,
-                                          bool use_share, int& k, TileInfo& t) {
+// edge tiles).  kPack, fprop / dgrad: where the last sweep over the XCDs has at most four chunks
+// left, two XCDs take each, a half of every tile's rows (Sched<2>) each.
+template <int MODE, bool kPack>
+__device__ __forceinline__ bool next_tile(const GemmArgs& g, int n_blocks, bool use_share, int& k, TileInfo& t) {
+  // fprop / dgrad: from the opaque block index, so that none of it stays in registers across the
+  // K loop (dgrad spilled two; wgrad has room, and is 1% slower with this)
+  int bid = blockIdx.x;
+  if (MODE != kWgrad) asm volatile("" : "+s"(bid));
+  const int n_slots = g.n_slots, group_size = 8 * n_slots;
+  const int group = bid / group_size, in_group = bid - group * group_size;
+  const int xcd = in_group & 7, slot = in_group >> 3, k_end = (group + 1) * kRoundsPerWg;
+  const int n_qg = !kPack ? 0 : MODE == kWgrad ? g.E * g.n_qt : __builtin_amdgcn_readfirstlane(g_cum[g.E]);
   for (; k < k_end; ++k) {
     const int i = k * n_slots + slot;
     if (MODE == kWgrad && use_share) {
@@ -832,14 +858,22 @@ __device__ __forceinline__ bool next_tile(const GemmArgs& g, int xcd, int slot, 
       decode_share_tile(g, xcd, i, t);
       return true;
     }
-    const int blk = (i / kPersistSlots) * 8 + xcd;
+    const int sweep = (i / kPersistSlots) * 8;
+    if (kPack && MODE != kWgrad && sweep == (n_blocks & ~7) && (n_blocks & 7) <= 4) {
+      if (xcd >= 2 * (n_blocks & 7)) return false;
+      if (!decode_tile<MODE, kPack>(g, n_qg, sweep + (xcd >> 1), i % kPersistSlots, t)) continue;
+      if (xcd & 1) t.q0 += kTQ / 2; else t.q_end = min(t.q_end, t.q0 + kTQ / 2);
+      if (t.q0 < t.q_end) return true;
+      continue;
+    }
+    const int blk = sweep + xcd;
     if (blk >= n_blocks) return false;
-    if (decode_tile<MODE>(g, blk, i % kPersistSlots, t)) return true;
+    if (decode_tile<MODE, kPack>(g, n_qg, blk, i % kPersistSlots, t)) return true;
   }
   return false;
 }
 
-template <int MODE, typename SC>
+template <int MODE, typename SC, bool kPack>
 __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
   const int tid = threadIdx.x;
   Tile<MODE, SC> T;
@@ -847,11 +881,6 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
   T.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   T.wp = T.wave & 1;
   T.wq = T.wave >> 1;
-  const int n_slots = g.n_slots, group_size = 8 * n_slots;
-  const int group = blockIdx.x / group_size, in_group = blockIdx.x - group * group_size;
-  const int xcd = in_group & 7, slot = in_group >> 3;
-  const int k_end = (group + 1) * kRoundsPerWg;
-
   int n_qg;  // q tiles
   if (MODE != kWgrad) {
     // cumulative 256-row tile counts and row offsets per expert: one wave, 64 per pass
@@ -900,10 +929,11 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
     __syncthreads();
     use_share = __builtin_amdgcn_readfirstlane(g_cum[0]) != 0;
   }
-  const int n_blocks = ((g.n_pt + kBP - 1) / kBP) * ((n_qg + kBQ - 1) / kBQ);
-  int k = group * kRoundsPerWg;
+  const int n_blocks = kPack ? (n_qg * g.n_pt + kPersistSlots - 1) / kPersistSlots
+                             : ((g.n_pt + kBP - 1) / kBP) * ((n_qg + kBQ - 1) / kBQ);
+  int k = (int)(blockIdx.x / (8 * g.n_slots)) * kRoundsPerWg;
   TileInfo t;
-  if (!next_tile<MODE>(g, xcd, slot, n_slots, n_blocks, k_end, use_share, k, t)) return;
+  if (!next_tile<MODE, kPack>(g, n_blocks, use_share, k, t)) return;
   setup_tile<MODE, SC>(T, g, t);
   if (T.nk > 0) dma_first_stage<MODE, SC>(T);
   // Loop invariant: tile t is set up, its stage 0 and scale batch 0 are in flight (if it
@@ -922,7 +952,7 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
     lds_barrier();  // every wave is done with the stage buffers and the scale batches
     TileInfo tn;
     ++k;
-    const bool more = next_tile<MODE>(g, xcd, slot, n_slots, n_blocks, k_end, use_share, k, tn);
+    const bool more = next_tile<MODE, kPack>(g, n_blocks, use_share, k, tn);
     if (more) {
       setup_tile<MODE, SC>(T, g, tn);
       if (T.nk > 0) dma_first_stage<MODE, SC>(T);  // buffer 0 and scale batch 0, under the epilogue
@@ -977,12 +1007,18 @@ static hipError_t grouped_gemm_impl(GemmMode mode, const uint8_t* a, const SC* a
     g.Np = N; g.Kdim = K;
     g.n_pt = (int)((N + kTP - 1) / kTP);
     grid = grid_blocks(blocks_of(g.n_pt, qt_bound), g.n_slots);
-    grouped_gemm_kernel<kFprop, SC><<<grid, kThreads, 0, st>>>(g);
+    if (g.n_pt % kBP != 0)
+      grouped_gemm_kernel<kFprop, SC, true><<<grid, kThreads, 0, st>>>(g);
+    else
+      grouped_gemm_kernel<kFprop, SC, false><<<grid, kThreads, 0, st>>>(g);
   } else if (mode == kDgrad) {  // out[m, k] = g[m, :] . w[e, :, k]
     g.Np = K; g.Kdim = N;
     g.n_pt = (int)((K + kTP - 1) / kTP);
     grid = grid_blocks(blocks_of(g.n_pt, qt_bound), g.n_slots);
-    grouped_gemm_kernel<kDgrad, SC><<<grid, kThreads, 0, st>>>(g);
+    if (g.n_pt % kBP != 0)
+      grouped_gemm_kernel<kDgrad, SC, true><<<grid, kThreads, 0, st>>>(g);
+    else
+      grouped_gemm_kernel<kDgrad, SC, false><<<grid, kThreads, 0, st>>>(g);
   } else {  // dw[e, n, k] = sum_m gT[n, m] xT[k, m]
     g.Np = K; g.Nq = N;
     g.n_pt = (int)((K + kTP - 1) / kTP);
@@ -1005,7 +1041,10 @@ static hipError_t grouped_gemm_impl(GemmMode mode, const uint8_t* a, const SC* a
     const int64_t blocks_items = (blocks_of(g.n_pt, (int64_t)E * g.n_qt) + 7) / 8 * kPersistSlots;
     const int64_t share_items = (int64_t)E * g.share;
     grid = grid_items(share_items > blocks_items ? share_items : blocks_items, g.n_slots);
-    grouped_gemm_kernel<kWgrad, SC><<<grid, kThreads, 0, st>>>(g);
+    if (g.n_pt % kBP != 0)
+      grouped_gemm_kernel<kWgrad, SC, true><<<grid, kThreads, 0, st>>>(g);
+    else
+      grouped_gemm_kernel<kWgrad, SC, false><<<grid, kThreads, 0, st>>>(g);
   }
   return hipGetLastError();
 }

@@ -654,6 +654,8 @@ ROW_TILE_CASES = {
     "small_grid_short": ([256, 144, 16], 640, 256),
     # enough 256-row tiles for every CU several times over, odd column tiles
     "large_grid": ([1024, 784], 22144, 384),
+    # 790 tiles: 24 chunks of 32, and one that two XCDs share by halves of its tiles
+    "large_grid_tail": ([1024, 784, 512], 20096, 384),
 }
 
 
@@ -690,6 +692,7 @@ TOKEN_CASES = {
     "short_rounds": ([640, 16, 528, 0, 1040, 128], 2048, 1920),
     "large_skewed": ([6000, 128, 0, 272], 4096, 4096),
     "large_uniform": ([1024, 912, 1040, 1024], 4096, 4096),
+    "large_odd_columns": ([1024, 912, 0, 1040, 1024], 2048, 1408),
 }
 
 
