@@ -5,13 +5,15 @@
 // expert the weights are read once and barely multiplied, and with a few K stages per tile the
 // output and the first loads are most of a tile's time.  A 256 x 256 tile with one workgroup per
 // CU does these in turn (first loads, K loop, output) and multiplies padding rows; here
-//   * tiles are 128 (p) x TQ (q) with TQ = 64 or 128, so a group of few rows wastes little;
-//   * two or three workgroups share a CU (66 or 50 KB of LDS each), so one's loads and output
+//   * tiles are 128 (p) x TQ (q) with TQ = 64 or 128, so a group of few rows wastes little (wgrad,
+//     whose sizes do not depend on the routing, also 256 x 128: a quarter less DMA per product);
+//   * two or three workgroups share a CU (50 to 66 KB of LDS each), so one's loads and output
 //     run under the other's products;
 //   * each workgroup walks its tiles as one stream of K stages: the DMA runs two stages ahead of
 //     the products across tile boundaries, so no tile waits for its first loads.
 // A stage's fragments are all read into registers, a barrier then frees its buffer and the DMA
-// of the stage after next goes into it while the MFMAs run: two buffers keep two stages in flight.
+// of the stage after next goes into it while the MFMAs run: two buffers keep two stages in flight
+// (256 x 128: one buffer, refilled under 1024 cycles of MFMAs and the other workgroup's).
 // The MFMA takes the q rows as its A operand, so a lane holds one output column and a store
 // instruction writes whole 128-byte runs of output rows straight from the accumulators.
 
@@ -22,21 +24,20 @@ namespace ff8 {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kTP = 128;  // p tile
 constexpr int kBW = 8;    // p tiles per block of the tile order
 
-template <int MODE, int TQ, typename SC>
+template <int MODE, int TP, int TQ, typename SC>
 struct Shape {
   static constexpr bool kE8 = sizeof(SC) == 1;
-  static constexpr int kWavesQ = 2, kWavesP = 2;
-  static constexpr int FP = kTP / kWavesP / 32, FQ = TQ / kWavesQ / 32;  // 32-wide fragments per wave
-  static constexpr int kPB = kTP * kBK, kQB = TQ * kBK, kStage = kPB + kQB;
-  static constexpr int kDmaP = kTP / 32, kDmaQ = TQ / 32, kDma = kDmaP + kDmaQ;  // per wave and stage
+  static constexpr int FP = TP / 64, FQ = TQ / 64;  // 32-wide fragments per wave, 2 x 2 waves
+  static constexpr int kBufs = TP == 256 ? 1 : 2;   // stage buffers
+  static constexpr int kPB = TP * kBK, kQB = TQ * kBK, kStage = kPB + kQB;
+  static constexpr int kDmaP = TP / 32, kDmaQ = TQ / 32, kDma = kDmaP + kDmaQ;  // per wave and stage
   // scale area of one batch (fprop / dgrad: four K blocks) or stage (wgrad): [P | Q]
-  static constexpr int kScaleP = (MODE == kWgrad) ? kTP * 4 : 256;
+  static constexpr int kScaleP = (MODE == kWgrad) ? TP * 4 : 256;
   static constexpr int kScaleQ = (MODE == kWgrad) ? 512 : TQ * 16;
   static constexpr int kScale = kScaleP + kScaleQ;
-  static constexpr int kScaleOff = 2 * kStage, kTabOff = kScaleOff + 2 * kScale;
+  static constexpr int kScaleOff = kBufs * kStage, kTabOff = kScaleOff + 2 * kScale;
   static constexpr int kPerCU = TQ == 128 ? 2 : 3;
   static constexpr int kStores = FQ * FP * (MODE == kWgrad ? 16 : 8);  // output stores of a wave's whole tile
 };
@@ -67,7 +68,7 @@ extern __shared__ __attribute__((aligned(1024))) uint8_t g_lds[];
 
 // Tile t (0 <= t < n) of the launch: experts in order, inside one blocks of kBW p tiles, each
 // block q tile by q tile, p fastest, so that workgroups running together share panels in L2.
-template <int MODE, int TQ>
+template <int MODE, int TP, int TQ>
 __device__ __forceinline__ TileAt tile_at(const GemmArgs& g, const int* cum, const int* off, int t) {
   TileAt a;
   int nq, rem;
@@ -94,7 +95,7 @@ __device__ __forceinline__ TileAt tile_at(const GemmArgs& g, const int* cum, con
   rem -= pb * kBW * nq;
   const int w = min(kBW, g.n_pt - pb * kBW);
   const int qt = rem / w;
-  a.p0 = (pb * kBW + rem - qt * w) * kTP;
+  a.p0 = (pb * kBW + rem - qt * w) * TP;
   a.k0 = 0;
   a.k_lo = 0;
   a.k_hi = kBK;
@@ -117,9 +118,9 @@ __device__ __forceinline__ TileAt tile_at(const GemmArgs& g, const int* cum, con
 }
 
 // The DMA side of a workgroup's stage stream.
-template <int MODE, int TQ, typename SC>
+template <int MODE, int TP, int TQ, typename SC>
 struct Stream {
-  using S = Shape<MODE, TQ, SC>;
+  using S = Shape<MODE, TP, TQ, SC>;
   i32x4 p_rsrc, q_rsrc, sp_rsrc, sq_rsrc;
   uint32_t p_voff, q_voff, sp_voff, sq_voff;  // lane offsets at the tile's K block 0
   uint32_t p_kstep, q_kstep, p_istep, q_istep, sp_kstep, sq_kstep;
@@ -135,15 +136,13 @@ struct Stream {
     if (MODE == kWgrad) {
       p_rsrc = make_rsrc(g.P, Np * M);
       q_rsrc = make_rsrc(g.Q, Nq * M);
-      // wave 0, 1: P scales; 2, 3: Q scales (UE8M0: waves 0 and 1; 2 and 3 repeat them)
-      const bool is_p = S::kE8 ? !(wave & 1) : wave < 2;
-      sp_rsrc = make_rsrc(is_p ? g.sP : g.sQ, (M / kTile) * (is_p ? Np : Nq) * sb);
-      sq_rsrc = sp_rsrc;
+      sp_rsrc = make_rsrc(g.sP, (M / kTile) * Np * sb);
+      sq_rsrc = make_rsrc(g.sQ, (M / kTile) * Nq * sb);
       p_kstep = Np * kBK;
       q_kstep = Nq * kBK;
       p_istep = q_istep = 32 * kBK;
-      sp_kstep = (is_p ? Np : Nq) * sb;
-      sq_kstep = 0;
+      sp_kstep = Np * sb;
+      sq_kstep = Nq * sb;
     } else {
       p_rsrc = make_rsrc(g.P, E * Np * Kd);
       q_rsrc = make_rsrc(g.Q, M * Kd);
@@ -161,7 +160,7 @@ struct Stream {
   // lane l row l / 8 of them, LDS chunk l % 8, so memory chunk (l % 8) ^ swizzle(row).
   __device__ __forceinline__ void setup(const GemmArgs& g, const int* cum, const int* off) {
     constexpr uint32_t sb = sizeof(SC);
-    const TileAt a = tile_at<MODE, TQ>(g, cum, off, t);
+    const TileAt a = tile_at<MODE, TP, TQ>(g, cum, off, t);
     ks = 0;
     nk = a.nk;
     k_lo = a.k_lo;
@@ -174,14 +173,12 @@ struct Stream {
       p_voff = (b0 * Np + p0 + r) * kBK + c;
       q_voff = (b0 * Nq + q0 + r) * kBK + c;
       c16 = (int)c;
-      if (S::kE8) {
-        const bool is_p = !(wave & 1);
-        sp_voff = b0 * (is_p ? Np : Nq) + (is_p ? p0 : q0) + 4 * (lane & 31);
-      } else {
-        const bool is_p = wave < 2;
-        const uint32_t row = (is_p ? p0 : q0) + (64 * (wave & 1) + lane) % (is_p ? kTP : TQ);
-        sp_voff = (b0 * (is_p ? Np : Nq) + row) * sb;
-      }
+      // one dword per lane: 64 rows of float32 scales per wave (each wave repeats another's past the
+      // tile), all rows of UE8M0 bytes (repeated likewise)
+      const uint32_t pr = S::kE8 ? 4 * (lane & (TP / 4 - 1)) : (64 * wave + lane) & (TP - 1);
+      const uint32_t qr = S::kE8 ? 4 * (lane & (TQ / 4 - 1)) : (64 * wave + lane) & (TQ - 1);
+      sp_voff = (b0 * Np + p0 + pr) * sb;
+      sq_voff = (b0 * Nq + q0 + qr) * sb;
       return;
     }
     q_voff = (q0 + r) * Kd + c;
@@ -203,13 +200,14 @@ struct Stream {
   __device__ __forceinline__ void produce(const GemmArgs& g) {
     if (t >= t_end) return;
     const uint32_t lds = (uint32_t)(uintptr_t)(lds_u8*)g_lds;
-    const uint32_t stage = lds + (uint32_t)(produced & 1) * S::kStage;
+    const uint32_t stage = lds + (S::kBufs == 1 ? 0 : (uint32_t)(produced & 1) * S::kStage);
     if (MODE == kWgrad || (ks & 3) == 0) {
       const uint32_t sc = lds + S::kScaleOff + (uint32_t)(batches & 1) * S::kScale;
       const uint32_t k = (uint32_t)ks;
       if (MODE == kWgrad) {
-        const uint32_t dst = S::kE8 ? (wave & 1) * S::kScaleP : (wave >= 2 ? S::kScaleP : 0) + (wave & 1) * 256;
-        dma4(sp_rsrc, sp_voff + k * sp_kstep, sc + dst);
+        const uint32_t pw = S::kE8 ? 0 : wave & (TP / 64 - 1), qw = S::kE8 ? 0 : wave & (TQ / 64 - 1);
+        dma4(sp_rsrc, sp_voff + k * sp_kstep, sc + pw * 256);
+        dma4(sq_rsrc, sq_voff + k * sq_kstep, sc + S::kScaleP + qw * 256);
       } else {
         dma4(sp_rsrc, sp_voff + k * sp_kstep, sc);
         if (S::kE8) {
@@ -249,12 +247,12 @@ struct Stream {
   }
 };
 
-template <int MODE, int TQ, typename SC>
-__global__ __launch_bounds__(kThreads, (Shape<MODE, TQ, SC>::kPerCU)) void grouped_gemm_small_kernel(GemmArgs g) {
-  using S = Shape<MODE, TQ, SC>;
+template <int MODE, int TP, int TQ, typename SC>
+__global__ __launch_bounds__(kThreads, (Shape<MODE, TP, TQ, SC>::kPerCU)) void grouped_gemm_small_kernel(GemmArgs g) {
+  using S = Shape<MODE, TP, TQ, SC>;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wp = wave / S::kWavesQ, wq = wave - wp * S::kWavesQ;
+  const int wp = wave >> 1, wq = wave & 1;
   const int l31 = lane & 31, h = lane >> 5;
   int* const off = reinterpret_cast<int*>(g_lds + S::kTabOff);  // row offsets of the experts
   int* const cum = off + g.E + 1;                               // fprop / dgrad: cumulative q tiles
@@ -298,7 +296,7 @@ __global__ __launch_bounds__(kThreads, (Shape<MODE, TQ, SC>::kPerCU)) void group
   const int lo = first + group * g.n_slots * g.rounds, hi = min(end, lo + g.n_slots * g.rounds);
   if (lo + slot >= hi) return;
 
-  Stream<MODE, TQ, SC> st;
+  Stream<MODE, TP, TQ, SC> st;
   st.wave = wave;
   st.lane = lane;
   st.t = lo + slot;
@@ -308,10 +306,10 @@ __global__ __launch_bounds__(kThreads, (Shape<MODE, TQ, SC>::kPerCU)) void group
   st.init(g);
   st.setup(g, cum, off);
   st.advance(g, cum, off);
-  st.produce(g);
-  st.advance(g, cum, off);
-  st.produce(g);
-  st.advance(g, cum, off);
+  for (int i = 0; i < S::kBufs; ++i) {
+    st.produce(g);
+    st.advance(g, cum, off);
+  }
 
   // lane addresses of the fragment reads within a stage
   int ra[4];  // K-major: 16-byte chunk 2 h + i of row l31 (i = 4 half-step + piece)
@@ -329,7 +327,7 @@ __global__ __launch_bounds__(kThreads, (Shape<MODE, TQ, SC>::kPerCU)) void group
 
   int stage_no = 0, batch_no = 0;
   int since = 2;  // stages consumed since this wave's last full output (2: two or more)
-  TileAt a = tile_at<MODE, TQ>(g, cum, off, lo + slot);
+  TileAt a = tile_at<MODE, TP, TQ>(g, cum, off, lo + slot);
   for (int t = lo + slot; t < hi; t += g.n_slots) {
     f32x16 acc[S::FQ][S::FP];
 #pragma unroll
@@ -342,10 +340,10 @@ __global__ __launch_bounds__(kThreads, (Shape<MODE, TQ, SC>::kPerCU)) void group
     for (int ks = 0; ks < a.nk; ++ks) {
       // this wave's DMA of the stage has landed when only younger ones are in flight (loads and
       // stores retire in order): the next stage's, and the previous tile's output if all its
-      // stores were issued after the stage's DMA, which is so for the two stages that follow it
-      wait_younger<S::kDma, S::kStores>(st.produced > stage_no + 1, since < 2);
+      // stores were issued after the stage's DMA, which is so for the kBufs stages that follow it
+      wait_younger<S::kDma, S::kStores>(st.produced > stage_no + 1, since < S::kBufs);
       if (since < 2) ++since;
-      const uint8_t* const P = g_lds + (stage_no & 1) * S::kStage;
+      const uint8_t* const P = g_lds + (S::kBufs == 1 ? 0 : (stage_no & 1) * S::kStage);
       const uint8_t* const Q = P + S::kPB;
       i32x8 fp[2][S::FP], fq[2][S::FQ];
 #pragma unroll
@@ -437,9 +435,13 @@ __global__ __launch_bounds__(kThreads, (Shape<MODE, TQ, SC>::kPerCU)) void group
       st.advance(g, cum, off);  // under the MFMAs
     }
     const TileAt done = a;
-    if (t + g.n_slots < hi) a = tile_at<MODE, TQ>(g, cum, off, t + g.n_slots);
+    if (t + g.n_slots < hi) a = tile_at<MODE, TP, TQ>(g, cum, off, t + g.n_slots);
     if (MODE == kWgrad && done.nk == 0 && g.accumulate) continue;
     since = done.q0 + 32 * S::FQ * (wq + 1) <= done.q_end ? 0 : 2;
+    if (TP == 256 && done.p0 + 128 * wp >= g.Np) {  // the wave's columns lie past the edge
+      since = 2;
+      continue;
+    }
     // Output: lane column p, register i row 8 (i / 4) + 4 h + i % 4 of a 32 x 32 fragment.  Group
     // ends are multiples of 16, so the 8 rows of a register quad are all inside or all outside.
 #pragma unroll
@@ -486,9 +488,9 @@ __global__ __launch_bounds__(kThreads, (Shape<MODE, TQ, SC>::kPerCU)) void group
   }
 }
 
-template <int MODE, int TQ, typename SC>
+template <int MODE, int TP, int TQ, typename SC>
 hipError_t run_small(GemmArgs g, int64_t tiles_max, hipStream_t st) {
-  using S = Shape<MODE, TQ, SC>;
+  using S = Shape<MODE, TP, TQ, SC>;
   const int lds = S::kTabOff + (MODE == kWgrad ? 1 : 2) * (g.E + 1) * (int)sizeof(int);
   const int64_t per_xcd = (tiles_max + 7) / 8;
   int64_t slots = (int64_t)(device_cu_count() / 8) * S::kPerCU;
@@ -496,7 +498,7 @@ hipError_t run_small(GemmArgs g, int64_t tiles_max, hipStream_t st) {
   if (slots > per_xcd) slots = per_xcd;
   g.n_slots = (int)slots;
   const int64_t groups = (per_xcd + slots * g.rounds - 1) / (slots * g.rounds);
-  grouped_gemm_small_kernel<MODE, TQ, SC><<<(unsigned)(groups * slots * 8), kThreads, lds, st>>>(g);
+  grouped_gemm_small_kernel<MODE, TP, TQ, SC><<<(unsigned)(groups * slots * 8), kThreads, lds, st>>>(g);
   return hipGetLastError();
 }
 
@@ -514,17 +516,23 @@ hipError_t grouped_gemm_small_impl(GemmMode mode, int tq, const uint8_t* a, cons
   g.Np = (int)(mode == kFprop ? N : K);
   g.Nq = (int)N;
   g.Kdim = (int)(mode == kFprop ? K : N);
-  g.n_pt = g.Np / kTP;
   if (mode == kWgrad) {
     g.n_qt = (int)(N / 128);
+    // 256 x 128 tiles where there are at least four per CU (16 experts of 2048 x 2048, 640 tokens:
+    // 82 us with 128 x 128, 69 with these; 32 experts of 4096 x 7168, 512 tokens: 1024 / 920); below,
+    // the small ones spread better (8 experts of 1024 x 256: 8.5 / 11.8)
+    const bool w256 = (int64_t)E * g.n_qt * ((K + 255) / 256) >= 4 * (int64_t)device_cu_count();
     g.rounds = M_cap <= 128 * (int64_t)E ? 1 : 4;
-    return run_small<kWgrad, 128, SC>(g, (int64_t)E * g.n_qt * g.n_pt, st);
+    g.n_pt = (int)(w256 ? (K + 255) / 256 : K / 128);
+    const int64_t n = (int64_t)E * g.n_qt * g.n_pt;
+    return w256 ? run_small<kWgrad, 256, 128, SC>(g, n, st) : run_small<kWgrad, 128, 128, SC>(g, n, st);
   }
+  g.n_pt = g.Np / 128;
   g.rounds = 2;
   const int64_t n = ((M_cap + tq - 1) / tq + E) * g.n_pt;  // every expert adds at most one partial q tile
   if (mode == kFprop)
-    return tq == 64 ? run_small<kFprop, 64, SC>(g, n, st) : run_small<kFprop, 128, SC>(g, n, st);
-  return tq == 64 ? run_small<kDgrad, 64, SC>(g, n, st) : run_small<kDgrad, 128, SC>(g, n, st);
+    return tq == 64 ? run_small<kFprop, 128, 64, SC>(g, n, st) : run_small<kFprop, 128, 128, SC>(g, n, st);
+  return tq == 64 ? run_small<kDgrad, 128, 64, SC>(g, n, st) : run_small<kDgrad, 128, 128, SC>(g, n, st);
 }
 
 }  // namespace
@@ -541,15 +549,15 @@ hipError_t grouped_gemm_small_impl(GemmMode mode, int tq, const uint8_t* a, cons
 //    large tiles; 1.27 us (dgrad 1.5) per stage of a round of 512 small ones.  TQ 64 when
 //    even 128 x 128 tiles do not reach every CU, or reach it once for a few stages (8 experts of
 //    1024 x 256 and 256 x 512 with 256 rows, dgrad: 6.6 and 10.2 with TQ 128, 4.6 and 8.3 with 64).
-//  * wgrad up to 640 tokens per expert (its K): four to five K stages do not hide a 256 KB output
-//    tile.  32 experts of 4096 x 7168: 128 tokens 732 / 700, 256 796 / 729, 512 1123 / 976, 1024
-//    1436 / 1493; also where 256 x 256 tiles fill less than 5/8 of the CUs (8 experts of
-//    1024 x 256, 2048 tokens: 27.6 / 16.3).
+//  * wgrad up to 832 tokens per expert (its K): six K stages do not hide a 256 KB output tile.
+//    32 experts of 4096 x 7168: 128 tokens 727 / 682, 256 795 / 686, 512 1112 / 920, 768 1287 /
+//    1166, 1024 1437 / 1364; 7168 x 2048: 512 538 / 505, 768 614 / 617, 1024 685 / 737; also where
+//    256 x 256 tiles fill less than 5/8 of the CUs (8 experts of 1024 x 256, 640 tokens: 19.2 / 8.5).
 int small_gemm_tile(GemmMode mode, int E, int64_t M_cap, int64_t N, int64_t K) {
   const int64_t cus = device_cu_count();
   if (mode == kWgrad) {
     const int64_t tiles = E * ((N + 255) / 256) * ((K + 255) / 256);  // 256 x 256
-    return M_cap <= 640 * (int64_t)E || 8 * tiles <= 5 * cus ? 128 : 0;
+    return M_cap <= 832 * (int64_t)E || 8 * tiles <= 5 * cus ? 128 : 0;
   }
   if (M_cap <= 64 * (int64_t)E) return 64;
   if (M_cap <= 96 * (int64_t)E) return 128;

@@ -684,12 +684,14 @@ def test_row_tile_shapes(mode, case):
     assert untouched(out[m:])
 
 
-# Token groups for wgrad: 128 x 128 tiles up to 640 tokens per expert, one or several tiles per
-# workgroup, and 256 x 256 tiles in both XCD orders above.
+# Token groups for wgrad: 128 x 128 tiles up to 832 tokens per expert, or 256 x 128 where those are
+# many, one or several tiles per workgroup; and 256 x 256 tiles in both XCD orders above.
 TOKEN_CASES = {
     "short_one_tile_each": ([16, 128, 0, 48], 2048, 2176),
     "short_empty_first": ([0, 0, 272, 400], 1152, 640),
     "short_rounds": ([640, 16, 528, 0, 1040, 128], 2048, 1920),
+    "wide_one_tile_each": ([16, 128, 0, 48], 4224, 2176),
+    "wide_rounds": ([640, 16, 528, 0, 1040, 128], 2816, 2176),
     "large_skewed": ([6000, 128, 0, 272], 4096, 4096),
     "large_uniform": ([1024, 912, 1040, 1024], 4096, 4096),
     "large_odd_columns": ([1024, 912, 0, 1040, 1024], 2048, 1408),
