@@ -652,6 +652,7 @@ ROW_TILE_CASES = {
     # few tiles of a longer contraction: a small grid, groups that end inside tiles
     "small_grid": ([512, 272], 1152, 1024),
     "small_grid_short": ([256, 144, 16], 640, 256),
+    "small_grid_wide": ([512, 272], 8192, 1152),
     # enough 256-row tiles for every CU several times over, odd column tiles
     "large_grid": ([1024, 784], 22144, 384),
     # 790 tiles: 24 chunks of 32, and one that two XCDs share by halves of its tiles
