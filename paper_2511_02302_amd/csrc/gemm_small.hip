@@ -74,9 +74,23 @@ __device__ __forceinline__ TileAt tile_at(const GemmArgs& g, const int* cum, con
   int nq, rem;
   if (MODE == kWgrad) {
     const int per = g.n_qt * g.n_pt;
-    a.e = t / per;
-    rem = t - a.e * per;
+    if (__builtin_amdgcn_readfirstlane(cum[0]) == 0) {
+      a.e = t / per;
+      rem = t - a.e * per;
+    } else {
+      // Shares: every XCD takes an eighth of every expert's tiles, so that their loads stay equal
+      // however the tokens are spread; eight experts in a row give each XCD another eighth (the
+      // parts are not exactly equal), which makes its tiles of a period one run, modulo per.
+      const int xcd = blockIdx.x & 7, period = t / per;
+      const int r0 = (xcd * per >> 3) + t - period * per;
+      rem = r0 < per ? r0 : r0 - per;
+      a.e = 8 * period + (((8 * rem + 7) / per - xcd) & 7);
+    }
     nq = g.n_qt;
+    if (a.e >= g.E) {  // shares, past the last expert of the last period
+      a.nk = 0;
+      return a;
+    }
   } else {
     int e = 0;  // experts whose tiles all come before t
     const int lane = threadIdx.x & 63;
@@ -255,9 +269,10 @@ __global__ __launch_bounds__(kThreads, (Shape<MODE, TP, TQ, SC>::kPerCU)) void g
   const int wp = wave >> 1, wq = wave & 1;
   const int l31 = lane & 31, h = lane >> 5;
   int* const off = reinterpret_cast<int*>(g_lds + S::kTabOff);  // row offsets of the experts
-  int* const cum = off + g.E + 1;                               // fprop / dgrad: cumulative q tiles
+  int* const cum = off + g.E + 1;  // fprop / dgrad: cumulative q tiles; wgrad: one flag, shares
 
   int n;  // tiles of the launch
+  bool shares = false;
   if (MODE != kWgrad) {
     if (tid < 64) {
       int carry = 0;
@@ -286,13 +301,28 @@ __global__ __launch_bounds__(kThreads, (Shape<MODE, TP, TQ, SC>::kPerCU)) void g
   } else {
     for (int i = tid; i <= g.E; i += kThreads) off[i] = g.offsets[i];
     __syncthreads();
-    n = g.E * g.n_qt * g.n_pt;
+    // Shares when the largest expert has over 64 rows more than 1.5 times the mean (every workgroup
+    // finds the same).  Zipf(1.2), 512 rows on average, 32 experts of 4096 x 7168: 1506 us by
+    // contiguous eighths, 892 by shares (256 x 256 tiles: 976).  With even routing the eighths share
+    // more panels in L2: 64 experts of 2816 x 2048, 256 rows each, 240 and 281.
+    if (tid < 64) {
+      int mx = 0;
+      for (int i = tid; i < g.E; i += 64) mx = max(mx, off[i + 1] - off[i]);
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) mx = max(mx, __shfl_xor(mx, d));
+      if (tid == 0) cum[0] = 2 * (int64_t)mx * g.E > 3 * (int64_t)(off[g.E] - off[0]) + 128 * (int64_t)g.E;
+    }
+    __syncthreads();
+    shares = __builtin_amdgcn_readfirstlane(cum[0]) != 0;
+    n = (shares ? (g.E + 7) / 8 : g.E) * g.n_qt * g.n_pt;  // shares: of one XCD
   }
   // XCD x (workgroups are dispatched round-robin over the 8) takes a contiguous eighth of the
   // tiles, group by group of `rounds` tiles for each of its n_slots running workgroups.
+  // (shares: its own tiles, an eighth of every expert's, see tile_at).
   const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
   const int group = local / g.n_slots, slot = local - group * g.n_slots;
-  const int first = xcd * (n >> 3) + min(xcd, n & 7), end = first + (n >> 3) + (xcd < (n & 7) ? 1 : 0);
+  const int first = shares ? 0 : xcd * (n >> 3) + min(xcd, n & 7);
+  const int end = shares ? n : first + (n >> 3) + (xcd < (n & 7) ? 1 : 0);
   const int lo = first + group * g.n_slots * g.rounds, hi = min(end, lo + g.n_slots * g.rounds);
   if (lo + slot >= hi) return;
 
@@ -436,7 +466,7 @@ __global__ __launch_bounds__(kThreads, (Shape<MODE, TP, TQ, SC>::kPerCU)) void g
     }
     const TileAt done = a;
     if (t + g.n_slots < hi) a = tile_at<MODE, TP, TQ>(g, cum, off, t + g.n_slots);
-    if (MODE == kWgrad && done.nk == 0 && g.accumulate) continue;
+    if (MODE == kWgrad && done.nk == 0 && (g.accumulate || done.e >= g.E)) continue;
     since = done.q0 + 32 * S::FQ * (wq + 1) <= done.q_end ? 0 : 2;
     if (TP == 256 && done.p0 + 128 * wp >= g.Np) {  // the wave's columns lie past the edge
       since = 2;
@@ -491,7 +521,7 @@ __global__ __launch_bounds__(kThreads, (Shape<MODE, TP, TQ, SC>::kPerCU)) void g
 template <int MODE, int TP, int TQ, typename SC>
 hipError_t run_small(GemmArgs g, int64_t tiles_max, hipStream_t st) {
   using S = Shape<MODE, TP, TQ, SC>;
-  const int lds = S::kTabOff + (MODE == kWgrad ? 1 : 2) * (g.E + 1) * (int)sizeof(int);
+  const int lds = S::kTabOff + (MODE == kWgrad ? g.E + 2 : 2 * (g.E + 1)) * (int)sizeof(int);
   const int64_t per_xcd = (tiles_max + 7) / 8;
   int64_t slots = (int64_t)(device_cu_count() / 8) * S::kPerCU;
   if (slots < 1) slots = 1;
@@ -524,7 +554,7 @@ hipError_t grouped_gemm_small_impl(GemmMode mode, int tq, const uint8_t* a, cons
     const bool w256 = (int64_t)E * g.n_qt * ((K + 255) / 256) >= 4 * (int64_t)device_cu_count();
     g.rounds = M_cap <= 128 * (int64_t)E ? 1 : 4;
     g.n_pt = (int)(w256 ? (K + 255) / 256 : K / 128);
-    const int64_t n = (int64_t)E * g.n_qt * g.n_pt;
+    const int64_t n = (int64_t)(E + 7) / 8 * 8 * g.n_qt * g.n_pt;  // whole periods of eight experts
     return w256 ? run_small<kWgrad, 256, 128, SC>(g, n, st) : run_small<kWgrad, 128, 128, SC>(g, n, st);
   }
   g.n_pt = g.Np / 128;

@@ -693,6 +693,8 @@ TOKEN_CASES = {
     "short_rounds": ([640, 16, 528, 0, 1040, 128], 2048, 1920),
     "wide_one_tile_each": ([16, 128, 0, 48], 4224, 2176),
     "wide_rounds": ([640, 16, 528, 0, 1040, 128], 2816, 2176),
+    # eleven experts (a period of eight and a part of one), an eighth of 108 tiles each per XCD
+    "wide_shares": ([16, 1200, 0, 48, 16, 0, 272, 16, 528, 16, 32], 1152, 2944),
     "large_skewed": ([6000, 128, 0, 272], 4096, 4096),
     "large_uniform": ([1024, 912, 1040, 1024], 4096, 4096),
     "large_odd_columns": ([1024, 912, 0, 1040, 1024], 2048, 1408),
