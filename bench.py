@@ -554,7 +554,8 @@ def cast_ops(torch, reps=20):
 def source_hash(stage):
     import hashlib
     h = hashlib.sha256()
-    for f in (STAGE_SOURCE[stage], "ff8_device.hpp"):
+    src = STAGE_SOURCE[stage]
+    for f in (src, "ff8_device.hpp") + (("gemm_shared.hpp",) if src == "gemm.hip" else ()):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
