@@ -42,19 +42,13 @@
 // that a tile's epilogue (output staged through one stage buffer, streaming stores)
 // overlaps the next tile's first-stage DMA into the other.
 
-#include "gemm_shared.hpp"
+#include "gemm_order.hpp"
 
 namespace ff8 {
 
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kTP = 256;   // p tile
-constexpr int kTQ = 256;   // q tile
-constexpr int kBQ = 8;     // q tiles per XCD block
-constexpr int kBP = 4;     // p tiles per XCD block
-constexpr int kPersistSlots = kBQ * kBP;  // workgroups per XCD and group
-static_assert(kPersistSlots == 32, "an XCD block is the 32 workgroups one XCD runs at once");
 constexpr int kTileBytes = kTP * kBK;  // 32 KB per operand per stage
 // Schedule of a stage for tiles with NB 32-row fragments of q per wave (4: 256 q rows; 2: a
 // group's last tile with at most 128 rows, see Tile).  MFMA slots and fragment reads of a
@@ -470,83 +464,6 @@ struct Tile {
   }
 };
 
-// One tile of the grouped product: expert e, q rows [q0, q_end) of a 256-row tile, p
-// columns from p0, contraction from k0 over nk stages.
-struct TileInfo {
-  int e, blk;
-  int q0, q_end, k0, p0, nk;  // rows, columns and stages all stay below 2^31
-  int k_lo, k_hi;             // wgrad: valid K bytes of the first / last stage
-};
-
-// wgrad: the K range of expert e's tiles.  K runs over whole 128-token blocks from the one
-// holding offsets[e]; with groups padded to 16 the first and last may be shared with
-// neighbouring experts (masked in their DMAs).
-__device__ __forceinline__ void wgrad_k_range(const GemmArgs& g, int e, TileInfo& t) {
-  const int o0 = __builtin_amdgcn_readfirstlane(g.offsets[e]);
-  const int o1 = __builtin_amdgcn_readfirstlane(g.offsets[e + 1]);
-  const int kb0 = o0 & ~(kBK - 1);
-  t.k0 = kb0;
-  t.nk = o1 > o0 ? (o1 - kb0 + kBK - 1) / kBK : 0;
-  t.k_lo = o0 - kb0;
-  t.k_hi = o1 > o0 ? o1 - (kb0 + (t.nk - 1) * kBK) : kBK;
-}
-
-// Tile w_in of XCD block blk (kBQ x kBP tiles, p fastest).  False for tiles past the
-// edges.  fprop/dgrad: q tiles are 256-row tiles of the expert groups (g_cum / g_off:
-// cumulative tile counts and row offsets per expert, in LDS); n_qg: q tiles of the launch.
-// kPack (p tiles not a multiple of kBP): every third or so block would be cut by the p edge and
-// leave its XCD a part of the work, so the blocks' tiles are packed into chunks of 32 in block
-// order, and blk is a chunk; every chunk but the last is full.  64 experts of 1024 rows, 2048 x
-// 1408 (6 p tiles): dgrad 254 -> 220 us, wgrad 364 -> 310.  With whole blocks only, the longer
-// lookup between two tiles costs 1-2%, so those keep the short one.
-template <int MODE, bool kPack>
-__device__ __forceinline__ bool decode_tile(const GemmArgs& g, int n_qg, int blk, int w_in, TileInfo& t) {
-  int qg, pt;  // global q-tile index, p tile
-  if constexpr (kPack) {
-    const int l = blk * kPersistSlots + w_in;
-    if (l >= n_qg * g.n_pt) return false;
-    const int row = l / (kBQ * g.n_pt), l_q = l - row * kBQ * g.n_pt;  // row of blocks
-    const int nq = min(kBQ, n_qg - row * kBQ);
-    const int pb = l_q / (kBP * nq), l_p = l_q - pb * kBP * nq;
-    const int np = min(kBP, g.n_pt - pb * kBP);
-    const int lq = l_p / np;
-    qg = row * kBQ + lq;
-    pt = pb * kBP + l_p - lq * np;
-  } else {
-    const int n_pb = (g.n_pt + kBP - 1) / kBP;
-    const int qb = blk / n_pb, pb = blk - qb * n_pb;
-    qg = qb * kBQ + w_in / kBP;
-    pt = pb * kBP + w_in % kBP;
-    if (pt >= g.n_pt) return false;
-  }
-  t.blk = blk;
-  t.p0 = (int64_t)pt * kTP;
-  if (MODE != kWgrad) {
-    if (qg >= g_cum[g.E]) return false;
-    int lo = 0, hi = g.E - 1;  // largest e with cum[e] <= qg
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (g_cum[mid] <= qg) lo = mid; else hi = mid - 1;
-    }
-    const int e = __builtin_amdgcn_readfirstlane(lo);
-    t.e = e;
-    t.q0 = __builtin_amdgcn_readfirstlane(g_off[e] + (qg - g_cum[e]) * kTQ);  // uniform (LDS values)
-    t.q_end = __builtin_amdgcn_readfirstlane(g_off[e + 1]);
-    t.k0 = 0;
-    t.nk = g.Kdim / kBK;
-    t.k_lo = 0;
-    t.k_hi = kBK;
-  } else {
-    if (qg >= g.E * g.n_qt) return false;
-    const int e = qg / g.n_qt;
-    t.e = e;
-    t.q0 = (int64_t)(qg - e * g.n_qt) * kTQ;
-    t.q_end = g.Nq;
-    wgrad_k_range(g, e, t);
-  }
-  return true;
-}
-
 // DMA sources of tile t: wave-uniform bases and resources, per-lane offsets (lane l of
 // tile DMA instruction i writes LDS bytes 16 l .. of that instruction's 1 KB).  Offsets are
 // 32-bit (the host keeps every operand under 4 GiB); past an operand's end they may wrap,
@@ -558,7 +475,7 @@ __device__ __forceinline__ void setup_tile(Tile<MODE, SC>& T, const GemmArgs& g,
   const uint32_t q0 = (uint32_t)t.q0, k0 = (uint32_t)t.k0, p0 = (uint32_t)t.p0;
   const uint32_t Np = (uint32_t)g.Np, Kdim = (uint32_t)g.Kdim, M_cap = (uint32_t)g.M_cap;
   T.nk = t.nk;
-  T.half = MODE != kWgrad && t.q_end - t.q0 <= 128;
+  T.half = MODE != kWgrad && half_tile(t);
   T.k_lo = t.k_lo;
   T.k_hi = t.k_hi;
   const uint32_t q_ld = (MODE == kWgrad) ? M_cap : Kdim;
@@ -792,87 +709,17 @@ __device__ __forceinline__ void k_loop(Tile<MODE, SC>& T) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the tail's reload DMAs have landed
 }
 
-// Semi-persistent: the grid is a sequence of groups of S workgroups per XCD (S = 32 on
-// 256 CUs, one workgroup per CU), and each workgroup runs kRoundsPerWg tiles.  Workgroups
-// are dispatched round-robin over the 8 XCDs, and in order within an XCD.  XCD x owns XCD
-// blocks x, x + 8, x + 16, ... (kBQ x kBP tiles each, p fastest); its work list is their
-// tiles in that order, item i = k S + s going to slot s of the group that owns round k.
-// With S = 32, slot s takes tile s of every block, so the 32 workgroups of an XCD work on
-// one block at a time and share its 8 q panels and 4 p panels per K step in their L2, while
-// the 8 XCDs together sweep one 16 x 16-tile window (about one expert).  Bounding a
-// workgroup to a few rounds keeps an XCD's workgroups from drifting apart (which costs L2
-// sharing) and lets faster CUs take more groups.
-// wgrad under skewed routing: every expert has the same tile count, so an expert's blocks
-// rarely divide evenly over the 8 XCDs, and the largest experts' extra blocks pile up on a
-// few of them.  When the largest expert has more than twice the mean rows (decided in every
-// workgroup from the offsets, identically), each XCD instead takes one of 8 equal rectangles
-// of every expert's tile grid (at least one round of 32 tiles each), which balances the XCDs
-// exactly; with near-uniform routing the blocks, which share more operand panels per round,
-// are kept.
-// Between tiles, the next tile's first stage (and scale batch) streams into stage buffer 0
-// while the finished tile's output is staged through buffer 1 and stored; its second
-// stage follows once the epilogue has left buffer 1.  All control flow is
-// workgroup-uniform (tile decode from uniform values), so every barrier is reached by all
-// four waves, and every wave leaves the tile loop with the same tile count.
-constexpr int kRoundsPerWg = 4;           // work rounds (tiles) per workgroup
-
 // Workgroup barrier that waits for this wave's LDS accesses only: global stores may stay in
 // flight across it (a __syncthreads fence would drain them).  One asm statement, so that
 // no memory access moves across the barrier.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// wgrad, expert-share schedule: item i of XCD x is tile l = i % share of expert e = i / share
-// in XCD x's rectangle (p fastest).  Every expert's tiles are split evenly over the 8 XCDs,
-// so the XCDs' loads stay equal however skewed the routing is (with XCD blocks, an expert's
-// block count is rarely a multiple of 8, and the largest experts' extra blocks pile up on a
-// few XCDs).
-__device__ __forceinline__ void decode_share_tile(const GemmArgs& g, int xcd, int i, TileInfo& t) {
-  const int e = i / g.share, l = i - e * g.share;
-  const int lq = l / g.rect_p, lp = l - lq * g.rect_p;
-  const int rq = xcd / g.rect_b, rp = xcd - rq * g.rect_b;
-  t.blk = 0;
-  t.e = e;
-  t.p0 = (rp * g.rect_p + lp) * kTP;
-  t.q0 = (rq * g.rect_q + lq) * kTQ;
-  t.q_end = g.Nq;
-  wgrad_k_range(g, e, t);
-}
-
-// Next tile of this workgroup from round k on, below round k_end (k advances past empty
-// edge tiles).  kPack, fprop / dgrad: where the last sweep over the XCDs has at most four chunks
-// left, two XCDs take each, a half of every tile's rows (Sched<2>) each.
-template <int MODE, bool kPack>
-__device__ __forceinline__ bool next_tile(const GemmArgs& g, int n_blocks, bool use_share, int& k, TileInfo& t) {
-  // fprop / dgrad: from the opaque block index, so that none of it stays in registers across the
-  // K loop (dgrad spilled two; wgrad has room, and is 1% slower with this)
-  int bid = blockIdx.x;
-  if (MODE != kWgrad) asm volatile("" : "+s"(bid));
-  const int n_slots = g.n_slots, group_size = 8 * n_slots;
-  const int group = bid / group_size, in_group = bid - group * group_size;
-  const int xcd = in_group & 7, slot = in_group >> 3, k_end = (group + 1) * kRoundsPerWg;
-  const int n_qg = !kPack ? 0 : MODE == kWgrad ? g.E * g.n_qt : __builtin_amdgcn_readfirstlane(g_cum[g.E]);
-  for (; k < k_end; ++k) {
-    const int i = k * n_slots + slot;
-    if (MODE == kWgrad && use_share) {
-      if (i >= g.E * g.share) return false;
-      decode_share_tile(g, xcd, i, t);
-      return true;
-    }
-    const int sweep = (i / kPersistSlots) * 8;
-    if (kPack && MODE != kWgrad && sweep == (n_blocks & ~7) && (n_blocks & 7) <= 4) {
-      if (xcd >= 2 * (n_blocks & 7)) return false;
-      if (!decode_tile<MODE, kPack>(g, n_qg, sweep + (xcd >> 1), i % kPersistSlots, t)) continue;
-      if (xcd & 1) t.q0 += kTQ / 2; else t.q_end = min(t.q_end, t.q0 + kTQ / 2);
-      if (t.q0 < t.q_end) return true;
-      continue;
-    }
-    const int blk = sweep + xcd;
-    if (blk >= n_blocks) return false;
-    if (decode_tile<MODE, kPack>(g, n_qg, blk, i % kPersistSlots, t)) return true;
-  }
-  return false;
-}
-
+// One workgroup per CU walks its tiles (gemm_order.hpp).
+// Between tiles, the next tile's first stage (and scale batch) streams into stage buffer 0
+// while the finished tile's output is staged through buffer 1 and stored; its second
+// stage follows once the epilogue has left buffer 1.  All control flow is
+// workgroup-uniform (tile decode from uniform values), so every barrier is reached by all
+// four waves, and every wave leaves the tile loop with the same tile count.
 template <int MODE, typename SC, bool kPack>
 __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
   const int tid = threadIdx.x;
@@ -929,11 +776,10 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
     __syncthreads();
     use_share = __builtin_amdgcn_readfirstlane(g_cum[0]) != 0;
   }
-  const int n_blocks = kPack ? (n_qg * g.n_pt + kPersistSlots - 1) / kPersistSlots
-                             : ((g.n_pt + kBP - 1) / kBP) * ((n_qg + kBQ - 1) / kBQ);
+  const int n_blocks = order_blocks<kPack>(g, n_qg);
   int k = (int)(blockIdx.x / (8 * g.n_slots)) * kRoundsPerWg;
   TileInfo t;
-  if (!next_tile<MODE, kPack>(g, n_blocks, use_share, k, t)) return;
+  if (!next_tile<MODE, kPack>(g, g_cum, g_off, blockIdx.x, n_blocks, use_share, k, t)) return;
   setup_tile<MODE, SC>(T, g, t);
   if (T.nk > 0) dma_first_stage<MODE, SC>(T);
   // Loop invariant: tile t is set up, its stage 0 and scale batch 0 are in flight (if it
@@ -952,7 +798,7 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
     lds_barrier();  // every wave is done with the stage buffers and the scale batches
     TileInfo tn;
     ++k;
-    const bool more = next_tile<MODE, kPack>(g, n_blocks, use_share, k, tn);
+    const bool more = next_tile<MODE, kPack>(g, g_cum, g_off, blockIdx.x, n_blocks, use_share, k, tn);
     if (more) {
       setup_tile<MODE, SC>(T, g, tn);
       if (T.nk > 0) dma_first_stage<MODE, SC>(T);  // buffer 0 and scale batch 0, under the epilogue
@@ -965,23 +811,6 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
     lds_barrier();  // buffer 1 is free for the next tile's second stage
   }
 }
-
-// Grid: groups of n_slots workgroups per XCD (one per CU, the same number on each of the
-// 8 XCDs, at most kPersistSlots), enough groups of kRoundsPerWg rounds for `items` tiles per
-// XCD, or for n_blocks_max XCD blocks (workgroups past the work actually present exit at once).
-unsigned grid_items(int64_t items, int& n_slots) {  // items: work items (tiles) per XCD
-  int cus = (device_cu_count() / 8) * 8;
-  if (cus > 8 * kPersistSlots) cus = 8 * kPersistSlots;
-  if (cus < 8) cus = 8;
-  n_slots = cus / 8;
-  const int64_t rounds = (items + n_slots - 1) / n_slots;
-  const int64_t groups = (rounds + kRoundsPerWg - 1) / kRoundsPerWg;
-  return (unsigned)((groups > 0 ? groups : 1) * 8 * n_slots);
-}
-unsigned grid_blocks(int64_t n_blocks_max, int& n_slots) {
-  return grid_items((n_blocks_max + 7) / 8 * kPersistSlots, n_slots);
-}
-int64_t blocks_of(int n_pt, int64_t n_qg) { return (int64_t)((n_pt + kBP - 1) / kBP) * ((n_qg + kBQ - 1) / kBQ); }
 
 }  // namespace
 
@@ -1006,7 +835,7 @@ static hipError_t grouped_gemm_impl(GemmMode mode, const uint8_t* a, const SC* a
   if (mode == kFprop) {  // out[m, n] = a[m, :] . w[e, n, :]
     g.Np = N; g.Kdim = K;
     g.n_pt = (int)((N + kTP - 1) / kTP);
-    grid = grid_blocks(blocks_of(g.n_pt, qt_bound), g.n_slots);
+    grid = grid_blocks(blocks_of(g.n_pt, qt_bound), device_cu_count(), g.n_slots);
     if (g.n_pt % kBP != 0)
       grouped_gemm_kernel<kFprop, SC, true><<<grid, kThreads, 0, st>>>(g);
     else
@@ -1014,7 +843,7 @@ static hipError_t grouped_gemm_impl(GemmMode mode, const uint8_t* a, const SC* a
   } else if (mode == kDgrad) {  // out[m, k] = g[m, :] . w[e, :, k]
     g.Np = K; g.Kdim = N;
     g.n_pt = (int)((K + kTP - 1) / kTP);
-    grid = grid_blocks(blocks_of(g.n_pt, qt_bound), g.n_slots);
+    grid = grid_blocks(blocks_of(g.n_pt, qt_bound), device_cu_count(), g.n_slots);
     if (g.n_pt % kBP != 0)
       grouped_gemm_kernel<kDgrad, SC, true><<<grid, kThreads, 0, st>>>(g);
     else
@@ -1040,7 +869,7 @@ static hipError_t grouped_gemm_impl(GemmMode mode, const uint8_t* a, const SC* a
     // either schedule may be chosen on the device: the grid covers both
     const int64_t blocks_items = (blocks_of(g.n_pt, (int64_t)E * g.n_qt) + 7) / 8 * kPersistSlots;
     const int64_t share_items = (int64_t)E * g.share;
-    grid = grid_items(share_items > blocks_items ? share_items : blocks_items, g.n_slots);
+    grid = grid_items(share_items > blocks_items ? share_items : blocks_items, device_cu_count(), g.n_slots);
     if (g.n_pt % kBP != 0)
       grouped_gemm_kernel<kWgrad, SC, true><<<grid, kThreads, 0, st>>>(g);
     else
