@@ -172,7 +172,9 @@ __host__ __device__ __forceinline__ bool next_tile(const GemmArgs& g, const int*
     if (kPack && MODE != kWgrad && sweep == (n_blocks & ~7) && (n_blocks & 7) <= 4) {
       if (xcd >= 2 * (n_blocks & 7)) return false;
       if (!decode_tile<MODE, kPack>(g, cum, off, n_qg, sweep + (xcd >> 1), i % kPersistSlots, t)) continue;
-      if (xcd & 1) t.q0 += kTQ / 2; else t.q_end = min(t.q_end, t.q0 + kTQ / 2);
+      // q_end is the group's end, not the tile's: the odd half ends with the tile
+      t.q0 += (xcd & 1) * (kTQ / 2);
+      t.q_end = min(t.q_end, t.q0 + kTQ / 2);
       if (t.q0 < t.q_end) return true;
       continue;
     }

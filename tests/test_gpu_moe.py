@@ -657,6 +657,8 @@ ROW_TILE_CASES = {
     "large_grid": ([1024, 784], 22144, 384),
     # 790 tiles: 24 chunks of 32, and one that two XCDs share by halves of its tiles
     "large_grid_tail": ([1024, 784, 512], 20096, 384),
+    # the same with eight K blocks, where fprop's K order differs from chunk to chunk
+    "large_grid_tail_rotated": ([1024, 784, 512], 20096, 1024),
 }
 
 
@@ -683,6 +685,32 @@ def test_row_tile_shapes(mode, case):
         if rows[e]:
             assert rel_frob(f64(out[off[e]:off[e + 1]]), want[off[e]:off[e + 1]]) < GEMM_TOL, e
     assert untouched(out[m:])
+
+
+@pytest.mark.parametrize("rows,cols", [([1024, 784, 512], 20096), ([384] * 20, 6912), ([512, 272, 0, 768] * 5, 6400)])
+@pytest.mark.parametrize("mode", ["fprop", "dgrad"])
+def test_split_last_sweep_repeats_bit_for_bit(mode, rows, cols):
+    """The same bits over outputs that held other values.  Column tiles that are no multiple of four,
+    one to four chunks in the last sweep over the XCDs (25, 34 and 28 chunks), groups of several
+    row tiles and eight K blocks, so that tiles of different chunks add in different orders."""
+    E, depth = len(rows), 1024
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    m = int(off[-1])
+    M_cap = -(-m // 128) * 128
+    N, K = (cols, depth) if mode == "fprop" else (depth, cols)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m)
+    codes = lambda *shape: torch.randint(0, 127, shape, generator=g, device="cuda", dtype=torch.uint8)
+    scales = lambda *shape: torch.exp2(torch.randint(-6, 3, shape, generator=g, device="cuda").float())
+    args = [codes(M_cap, depth), scales(M_cap, depth // 128), codes(E, N, K), scales(E, N // 128, K // 128),
+            dev(torch.from_numpy(off))]
+    outs = []
+    for fill in (0x00, 0x7F, 0xFF):
+        out = torch.full((M_cap, 2 * cols), fill, dtype=torch.uint8, device="cuda").view(torch.bfloat16)
+        getattr(ff8, f"ff8_grouped_gemm_{mode}")(*args, out)
+        outs.append(out.view(torch.int16)[:m])
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
 
 
 # Token groups for wgrad: 128 x 128 tiles up to 832 tokens per expert, or 256 x 128 where those are

@@ -1,0 +1,91 @@
+"""The 256 x 256 GEMM's tile order covers every output row and column exactly once (CPU only).
+
+Two workgroups that store the same rows race, and fprop's K rotation follows the XCD block, so the
+bits that stay would depend on timing.  tile_order.cpp walks the kernel's own order on the host.
+"""
+
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2511_02302_amd import build as ff8_build
+
+SRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tile_order.cpp")
+
+
+@pytest.fixture(scope="module")
+def walk(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("order") / "order.so")
+    cmd = [ff8_build.hipcc()] + ff8_build.COMMON + ["-x", "hip", "--cuda-host-only", "-shared", SRC, "-o", lib]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    fn = ctypes.CDLL(lib).tile_order_walk
+    fn.restype = ctypes.c_long
+    fn.argtypes = [ctypes.c_int, ctypes.c_void_p] + [ctypes.c_int] * 4 + [ctypes.c_void_p, ctypes.c_long]
+
+    def tiles(rows, n_pt, n_qt=0, cus=256):
+        off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+        cap = 4 * (sum(-(-r // 256) for r in rows) + len(rows) * n_qt + 8) * n_pt
+        out = np.empty((cap, 6), np.int32)
+        n = fn(len(rows), off.ctypes.data, int(off[-1]), n_pt, n_qt, cus, out.ctypes.data, cap)
+        assert n >= 0
+        return off, out[:n]
+
+    return tiles
+
+
+def _routing(rng):
+    """Rows per expert as a routing gives them: even or skewed, padded to 16 or 128, empty ones."""
+    E = int(rng.integers(1, 130))
+    mean = float(np.exp(rng.uniform(np.log(8), np.log(1500))))
+    p = rng.permutation(np.arange(1, E + 1) ** -1.2) if rng.random() < 0.4 else np.ones(E)
+    rows = rng.poisson(np.minimum(mean * E * p / p.sum(), 8000))
+    rows[rng.random(E) < 0.1] = 0
+    align = int(rng.choice([16, 128]))
+    return ((rows + align - 1) // align * align).tolist()
+
+
+def _check_rows(walk, rows, n_pt, cus=256):
+    off, t = walk(rows, n_pt, cus=cus)
+    e, q0, q1, p0 = t[:, 0], t[:, 1], t[:, 2], t[:, 3]
+    assert np.all((off[e] <= q0) & (q0 < q1) & (q1 <= off[e + 1])), "rows of another group"
+    assert np.all((p0 % 256 == 0) & (p0 < 256 * n_pt))
+    bands = off[-1] // 16  # groups are multiples of 16 rows
+    writes = np.zeros((bands + 1, n_pt), np.int64)  # +1 where a tile begins, -1 past its end
+    assert np.all(q0 % 16 == 0) and np.all(q1 % 16 == 0)
+    np.add.at(writes, (q0 // 16, p0 // 256), 1)
+    np.add.at(writes, (q1 // 16, p0 // 256), -1)
+    count = np.cumsum(writes, axis=0)[:bands]
+    assert np.all(count == 1), f"{int((count > 1).sum())} bands written twice, {int((count == 0).sum())} never"
+
+
+@pytest.mark.parametrize("n_pt", [1, 2, 3, 4, 5, 6, 8, 11, 16, 28, 87])
+def test_row_tiles_cover_every_output_once(walk, n_pt):
+    rng = np.random.default_rng(n_pt)
+    for _ in range(60):
+        _check_rows(walk, _routing(rng), n_pt, cus=int(rng.choice([256, 256, 128, 304])))
+
+
+@pytest.mark.parametrize("rows,n_pt", [
+    ([384] * 64, 11),          # 44 chunks: four left for the last sweep
+    ([1024, 784, 512], 79),    # 25 chunks: one left
+    ([272, 0, 16, 528, 256], 11), ([4096], 3), ([512] * 19, 7)])
+def test_split_last_sweep_covers_every_output_once(walk, rows, n_pt):
+    _check_rows(walk, rows, n_pt)
+    off, t = walk(rows, n_pt)
+    chunks = -(-sum(-(-r // 256) for r in rows) * n_pt // 32)
+    last = t[t[:, 4] >= chunks // 8 * 8]
+    assert 1 <= chunks % 8 <= 4 and len(last)
+    # the last sweep's tiles are halves: no workgroup of it stores more than 128 rows
+    assert np.all(last[:, 2] - last[:, 1] <= 128)
+
+
+@pytest.mark.parametrize("n_pt,n_qt", [(1, 1), (3, 5), (4, 8), (11, 16), (16, 28), (28, 16)])
+def test_wgrad_blocks_cover_every_tile_once(walk, n_pt, n_qt):
+    rows = [128, 0, 1024, 16, 528]
+    _, t = walk(rows, n_pt, n_qt)
+    got = sorted(map(tuple, t[:, [0, 1, 3]].tolist()))
+    assert got == [(e, 256 * q, 256 * p) for e in range(len(rows)) for q in range(n_qt) for p in range(n_pt)]
