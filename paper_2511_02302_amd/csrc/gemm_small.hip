@@ -17,6 +17,7 @@
 // The MFMA takes the q rows as its A operand, so a lane holds one output column and a store
 // instruction writes whole 128-byte runs of output rows straight from the accumulators.
 
+#include "gemm_rule.hpp"
 #include "gemm_shared.hpp"
 
 namespace ff8 {
@@ -567,47 +568,8 @@ hipError_t grouped_gemm_small_impl(GemmMode mode, int tq, const uint8_t* a, cons
 
 }  // namespace
 
-// Which tiles a product takes.  M_cap / E bounds the mean rows of a group from above (it counts
-// the padding), the rest is known exactly.  Times below: us, 256 x 256 tiles / these tiles, on
-// normally distributed operands (random bytes draw more power, which slows the large tiles most).
-//  * fprop, dgrad, up to 96 rows per group, so one tile of rows per expert: both kernels stream the
-//    weights, the large tiles in whole rounds of one tile per CU (1.45 us per K stage, 3.5 us per
-//    round and 4.5 us once), these at 5.6 MB/us (fprop) or 4.75 (dgrad, whose loads are 128-byte
-//    runs of the weight's rows) with TQ 64 and 4.7 or 4.25 with TQ 128, which groups above 64 rows
-//    need.  The cheaper of the two: 16 rows, 32 experts of 4096 x 7168: fprop 174 / 163, dgrad 201 /
-//    198; 7168 x 2048: 101 / 85, 89 / 97; 64 experts of 2816 x 2048: 80 / 71, 73 / 82; 2048 x 1408: 42 /
-//    37, 52 / 37; 64 rows: 178 / 194, 208 / 224; 107 / 98, 91 / 106; 85 / 83, 76 / 89; 44 / 44, 54 / 43.
-//  * fprop, dgrad on grids of at most three 256 x 256 tiles per CU, where whole rounds of such
-//    tiles leave CUs idle: the same model of the large tiles against 1.42 us (dgrad 1.55) per stage
-//    of a round of 512 small ones.  16 experts of 2048 x 2048: 192 rows 32 / 22, 256 30 / 30, 512
-//    52 / 49, 1024 80 / 82; 8 of 4096 x 7168, fprop: 112 rows 78 / 53, 192 92 / 85, 512 158 / 173;
-//    dgrad: 192 rows 62 / 102.  TQ 64 when even 128 x 128 tiles do not reach every CU, or
-//    reach it once for a few stages (8 experts of 1024 x 256 and 256 x 512 with 256 rows, dgrad: 6.6
-//    and 10.2 with TQ 128, 4.6 and 8.3 with 64).
-//  * wgrad up to 832 tokens per expert (its K): six K stages do not hide a 256 KB output tile.
-//    32 experts of 4096 x 7168: 128 tokens 727 / 682, 256 795 / 686, 512 1112 / 920, 768 1287 /
-//    1166, 1024 1437 / 1364; 7168 x 2048: 512 538 / 505, 768 614 / 617, 1024 685 / 737; also where
-//    256 x 256 tiles fill less than 5/8 of the CUs (8 experts of 1024 x 256, 640 tokens: 19.2 / 8.5).
 int small_gemm_tile(GemmMode mode, int E, int64_t M_cap, int64_t N, int64_t K) {
-  const int64_t cus = device_cu_count();
-  if (mode == kWgrad) {
-    const int64_t tiles = E * ((N + 255) / 256) * ((K + 255) / 256);  // 256 x 256
-    return M_cap <= 832 * (int64_t)E || 8 * tiles <= 5 * cus ? 128 : 0;
-  }
-  const int64_t Np = mode == kFprop ? N : K, Kd = mode == kFprop ? K : N, nk = Kd / kBK;
-  const bool f = mode == kFprop;
-  // hundredths of a microsecond for n tiles of 256 x 256
-  auto t_large = [&](int64_t n) { return (n + cus - 1) / cus * (145 * nk + 350) + 450; };
-  if (M_cap <= 96 * (int64_t)E) {
-    const int tq = M_cap <= 64 * (int64_t)E ? 64 : 128;
-    const int64_t rate = tq == 64 ? (f ? 56000 : 47500) : (f ? 47000 : 42500);  // bytes per 0.01 us
-    return E * Np * Kd / rate + 200 < t_large(E * ((Np + 255) / 256)) ? tq : 0;
-  }
-  // q tiles: the rows' own and a share of one per expert for the groups' last, partial tiles
-  const int64_t large = (M_cap / 256 + (E + 7) / 8) * ((Np + 255) / 256);
-  const int64_t small = (M_cap / 128 + (E + 7) / 8) * (Np / 128);
-  if (large > 3 * cus || small * (f ? 142 : 155) * nk / (2 * cus) + 700 >= t_large(large)) return 0;
-  return small < cus || (small < 2 * cus && nk <= 8) ? 64 : 128;
+  return small_gemm_tile(mode, E, M_cap, N, K, device_cu_count());
 }
 
 hipError_t launch_grouped_gemm_small(GemmMode mode, int tq, const uint8_t* a, const float* a_s, const uint8_t* b,

@@ -1,7 +1,9 @@
-"""The 256 x 256 GEMM's tile order covers every output row and column exactly once (CPU only).
+"""Which tiles the grouped GEMMs run, and in which order (CPU only; tile_order.cpp compiles the
+library's own functions for the host).
 
-Two workgroups that store the same rows race, and fprop's K rotation follows the XCD block, so the
-bits that stay would depend on timing.  tile_order.cpp walks the kernel's own order on the host.
+The 256 x 256 tiles cover every output row and column exactly once: two workgroups that store the
+same rows race, and fprop's K rotation follows the XCD block, so the bits that stay would depend on
+timing.  The choice between them and the small tiles is the faster one at measured sizes.
 """
 
 import ctypes
@@ -17,12 +19,17 @@ SRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tile_order.cpp")
 
 
 @pytest.fixture(scope="module")
-def walk(tmp_path_factory):
+def host_lib(tmp_path_factory):
     lib = str(tmp_path_factory.mktemp("order") / "order.so")
     cmd = [ff8_build.hipcc()] + ff8_build.COMMON + ["-x", "hip", "--cuda-host-only", "-shared", SRC, "-o", lib]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
-    fn = ctypes.CDLL(lib).tile_order_walk
+    return ctypes.CDLL(lib)
+
+
+@pytest.fixture(scope="module")
+def walk(host_lib):
+    fn = host_lib.tile_order_walk
     fn.restype = ctypes.c_long
     fn.argtypes = [ctypes.c_int, ctypes.c_void_p] + [ctypes.c_int] * 4 + [ctypes.c_void_p, ctypes.c_long]
 
@@ -89,3 +96,23 @@ def test_wgrad_blocks_cover_every_tile_once(walk, n_pt, n_qt):
     _, t = walk(rows, n_pt, n_qt)
     got = sorted(map(tuple, t[:, [0, 1, 3]].tolist()))
     assert got == [(e, 256 * q, 256 * p) for e in range(len(rows)) for q in range(n_qt) for p in range(n_pt)]
+
+
+# Measured on one MI355X, operands in no cache: us with 256 x 256 tiles, us with the small ones.
+FPROP, DGRAD, WGRAD = 0, 1, 2
+
+
+@pytest.mark.parametrize("mode,E,M_cap,N,K,small", [
+    # groups of whole tiles: the large tiles' count is the rows', with no share for partial ones
+    (FPROP, 8, 8 * 512, 4096, 7168, 0),        # 97 / 148
+    (FPROP, 16, 16 * 512, 2048, 2048, 0),      # 39 / 52
+    (FPROP, 16, 16 * 384, 2048, 2048, 0),      # 34 / 40
+    (FPROP, 16, 16 * 192, 2048, 2048, 128),    # 37 / 31
+    (FPROP, 16, 16 * 256, 2048, 2048, 128),    # 40 / 32
+    (FPROP, 8, 8 * 192, 4096, 7168, 128),      # 96 / 84
+    (FPROP, 8, 8 * 256, 1024, 1024, 64),       # 24 / 12
+    (DGRAD, 16, 16 * 192, 6912, 1024, 64),     # 88 / 52
+])
+def test_tile_shape_choice(host_lib, mode, E, M_cap, N, K, small):
+    args = [ctypes.c_int64(v) for v in (M_cap, N, K, 256)]
+    assert host_lib.tile_rule(mode, E, *args) == small

@@ -1,6 +1,8 @@
-// Host walk of the 256 x 256 GEMM's tile order, for test_tile_order.py: every tile of every
-// workgroup of a launch, as the kernel's own functions give them.
+// Host side of the grouped GEMMs' tiles, for test_tile_order.py: the choice of the tile shape, and a
+// walk of the 256 x 256 tiles' order, every tile of every workgroup of a launch, as the kernel's own
+// functions give them.
 #include "gemm_order.hpp"
+#include "gemm_rule.hpp"
 
 namespace {
 
@@ -42,4 +44,8 @@ extern "C" long tile_order_walk(int E, const int* offsets, int m_cap, int n_pt, 
                         : walk<ff8::kWgrad, false>(g, cum, offsets, grid, n_qg, out, cap);
   return pack ? walk<ff8::kFprop, true>(g, cum, offsets, grid, n_qg, out, cap)
               : walk<ff8::kFprop, false>(g, cum, offsets, grid, n_qg, out, cap);
+}
+
+extern "C" int tile_rule(int mode, int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus) {
+  return ff8::small_gemm_tile((ff8::GemmMode)mode, E, M_cap, N, K, cus);
 }
