@@ -14,10 +14,12 @@ namespace ff8 {
 //    weights, the large tiles in whole rounds of one tile per CU (1.45 us per K stage, 3.5 us per
 //    round and 4.5 us once), these at 5.6 MB/us (fprop) or 4.75 (dgrad, whose loads are 128-byte
 //    runs of the weight's rows) with TQ 64 and 4.7 or 4.25 with TQ 128, which groups above 64 rows
-//    need.  The cheaper of the two: 16 rows, 32 experts of 4096 x 7168: fprop
-//    174 / 166, dgrad 205 / 205; 8 of them: 74 / 47, 53 / 59; 32 of 7168 x 2048: 106 / 90, 95 / 101; 64
-//    of 2816 x 2048: 85 / 75, 77 / 86; of 2048 x 1408: 46 / 40, 56 / 40; 64 rows: 183 / 175, 213 / 214;
-//    79 / 49, 56 / 59; 109 / 94, 95 / 104; 87 / 79, 79 / 88; 48 / 42, 58 / 42.
+//    need.  The cheaper of the two, for dgrad by a sixteenth (where they come closer the small tiles
+//    gain nothing, and a skewed routing costs them more: 32 experts of 4096 x 7168, 256 tokens x 4,
+//    Zipf(1.2): 104 / 125): 16 rows, 32 experts of 4096 x 7168: fprop 174 / 166, dgrad 205 / 205; 8 of
+//    them: 74 / 47, 53 / 59; 32 of 7168 x 2048: 106 / 90, 95 / 101; 64 of 2816 x 2048: 85 / 75, 77 / 86;
+//    of 2048 x 1408: 46 / 40, 56 / 40; 64 rows: 183 / 175, 213 / 214; 79 / 49, 56 / 59; 109 / 94, 95 /
+//    104; 87 / 79, 79 / 88; 48 / 42, 58 / 42.
 //  * fprop, dgrad on grids of at most three 256 x 256 tiles per CU, where whole rounds of such
 //    tiles leave CUs idle: the same model of the large tiles against 1.42 us (dgrad 1.55) per stage
 //    of a round of 512 small ones.  How many tiles the groups' last, partial ones add is not known
@@ -44,7 +46,7 @@ inline int small_gemm_tile(GemmMode mode, int E, int64_t M_cap, int64_t N, int64
     const int tq = M_cap <= 64 * (int64_t)E ? 64 : 128;
     const int64_t rate = tq == 64 ? (f ? 56000 : 47500) : (f ? 47000 : 42500);  // bytes per 0.01 us
     const int64_t small = E * Np * Kd / rate + 200, large = t_large(E * ((Np + 255) / 256));
-    return small < large ? tq : 0;
+    return (f ? small : small + small / 16) < large ? tq : 0;
   }
   // q tiles: the rows' own, and a share of one per expert for the groups' last, partial tiles
   const int64_t q_large = (M_cap + 255) / 256, n_pt = (Np + 255) / 256;

@@ -112,6 +112,13 @@ FPROP, DGRAD, WGRAD = 0, 1, 2
     (FPROP, 8, 8 * 192, 4096, 7168, 128),      # 96 / 84
     (FPROP, 8, 8 * 256, 1024, 1024, 64),       # 24 / 12
     (DGRAD, 16, 16 * 192, 6912, 1024, 64),     # 88 / 52
+    # a few rows per group
+    (DGRAD, 8, 8 * 16, 4096, 7168, 0),         # 53 / 59
+    (DGRAD, 32, 32 * 48, 4096, 7168, 0),       # 205 / 205; skewed 104 / 125
+    (DGRAD, 32, 32 * 16, 7168, 2048, 0),       # 95 / 101
+    (DGRAD, 64, 64 * 16, 2048, 1408, 64),      # 56 / 40
+    (FPROP, 32, 32 * 16, 7168, 2048, 64),      # 106 / 90
+    (FPROP, 8, 8 * 96, 4096, 7168, 128),       # 80 / 57
 ])
 def test_tile_shape_choice(host_lib, mode, E, M_cap, N, K, small):
     args = [ctypes.c_int64(v) for v in (M_cap, N, K, 256)]
