@@ -5,6 +5,46 @@
 
 namespace ff8 {
 
+// wgrad on the small tiles: 256 (K) x 128 (N) ones, or 128 x 128.  Two of either run on a CU.  Where at
+// most two of the first come to a CU, all run at once and need no second round as twice as many of the
+// others do, which pays from about four K stages on (us, 128 x 128 / 256 x 128: two per CU, 4 experts of
+// 2048 x 2048, 512 tokens 28 / 23, 768 33 / 27, 16 of 1024 x 1024 30 / 24, 35 / 28; 1.5 per CU, 8 experts of
+// 768 x 2048, 512 tokens 20 / 21, 12 of 512 x 2048, 1024 tokens 29 / 28).  A part of a second round costs
+// them a whole one (9 experts of 1024 x 2048, 2.25 per CU, 512 tokens 27 / 30; 10 of them, 2.5 per CU, 256
+// tokens 23 / 25); from three per CU on they move a quarter less (12 of 1024 x 2048, 512 tokens 37 / 33;
+// 15: 46 / 40; 16 of 2048 x 2048, 640 tokens 82 / 69; 32 of 4096 x 7168, 512 tokens 1024 / 920).
+inline int64_t wgrad_tiles256(int E, int64_t N, int64_t K) { return E * (N / 128) * ((K + 255) / 256); }
+inline bool wgrad_wide(int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus) {
+  const int64_t n = wgrad_tiles256(E, N, K);
+  return n >= 3 * cus || (n > cus && n <= 2 * cus && M_cap >= (4 * n >= 7 * cus ? 512 : 640) * (int64_t)E);
+}
+// wgrad on the small tiles or on 256 x 256 ones: six K stages of 128 tokens do not hide a 256 KB output
+// tile, eight nearly do.  M_cap / E is the tokens per expert.  Times: us, 256 x 256 / small tiles.
+//  * At most one 256 x 128 tile per CU: the small ones, whose products spread over twice the CUs (8
+//    experts of 640 x 1024, 256 tokens 20 / 11, 4096 60 / 44).
+//  * Below four per CU, up to 1024 tokens: the small ones (5 experts of 2048 x 1024, 1024 tokens 29 /
+//    26, 2048 40 / 38, 4096 61 / 64; 15 of 1024 x 2048, 1024 tokens 53 / 53).
+//  * Above, up to 1024 tokens, the cheaper by two lines in the K stages, us: 12.9 + 1.33 per stage for
+//    a round of the CUs with the large tiles, which take whole rounds, and for 512 of the 256 x 128
+//    ones 11.5 + 1.6, or 9.4 + 1.57 for outputs of at least 3584 columns.  7168 x 2048, 32 experts:
+//    384 tokens 467 / 436, 512 509 / 512, 640 550 / 569, 768 583 / 613; 64 of 2816 x 2048: 384 383 /
+//    344, 512 413 / 399, 768 471 / 477, 766 on average 474 / 510; 16 of 2816 x 2048 (5.5 rounds): 512 116 /
+//    106, 768 131 / 122; 64 of 2048 x 1408: 768 262 / 246; 32 of 4096 x 7168: 512 1059 / 872, 768 1212 /
+//    1050, 1024 1358 / 1226; of 7168 x 4096: 640 1165 / 959, 896 1329 / 1134.  Above 1024 tokens the
+//    gain under even routing (1280 tokens, 4096 x 7168: 1509 / 1405) is a loss under skewed
+//    (1443 / 1483).
+inline bool wgrad_small(int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus) {
+  const int64_t n = wgrad_tiles256(E, N, K);
+  if (n <= cus) return true;
+  if (M_cap > 1024 * (int64_t)E) return false;
+  if (n < 4 * cus) return true;
+  const int64_t rows = M_cap / E;  // 128 per stage; hundredths of a microsecond below
+  const int64_t large = ((N + 255) / 256) * ((K + 255) / 256) * E;
+  const int64_t t_large = (large + cus - 1) / cus * (1290 + 133 * rows / 128) + 600;
+  const int64_t per_round = K >= 3584 ? 940 + 157 * rows / 128 : 1150 + 160 * rows / 128;
+  return E * (N / 128) * (K / 128) * per_round / (4 * cus) + 540 < t_large;  // K / 128 / 2 tiles, half ones as halves
+}
+
 // The tq of the small tiles (64 or 128; wgrad: 128), or 0 for the 256 x 256 tiles; cus: compute
 // units of the device.  M_cap / E bounds the mean rows of a group from above (it counts the
 // padding), the rest is known exactly.  Times below: us, 256 x 256 tiles / these tiles, on normally
@@ -29,15 +69,9 @@ namespace ff8 {
 //    of 4096 x 7168: 192 rows 96 / 84; dgrad: 192 rows 67 / 105.  TQ 64 when even 128 x 128 tiles do not
 //    reach every CU, or reach it once for a few stages (8 experts of 1024 x 1024, 256 rows: 14.0 with
 //    TQ 128, 12.1 with 64).
-//  * wgrad up to 832 tokens per expert (its K): six K stages do not hide a 256 KB output tile.
-//    32 experts of 4096 x 7168: 128 tokens 727 / 682, 256 795 / 686, 512 1112 / 920, 768 1287 /
-//    1166, 1024 1437 / 1364; 7168 x 2048: 512 538 / 505, 768 614 / 617, 1024 685 / 737; also where
-//    256 x 256 tiles fill less than 5/8 of the CUs (8 experts of 1024 x 256, 640 tokens: 19.2 / 8.5).
+//  * wgrad: see wgrad_small.
 inline int small_gemm_tile(GemmMode mode, int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus) {
-  if (mode == kWgrad) {
-    const int64_t tiles = E * ((N + 255) / 256) * ((K + 255) / 256);  // 256 x 256
-    return M_cap <= 832 * (int64_t)E || 8 * tiles <= 5 * cus ? 128 : 0;
-  }
+  if (mode == kWgrad) return wgrad_small(E, M_cap, N, K, cus) ? 128 : 0;
   const int64_t Np = mode == kFprop ? N : K, Kd = mode == kFprop ? K : N, nk = Kd / kBK;
   const bool f = mode == kFprop;
   // hundredths of a microsecond for n tiles of 256 x 256

@@ -549,10 +549,7 @@ hipError_t grouped_gemm_small_impl(GemmMode mode, int tq, const uint8_t* a, cons
   g.Kdim = (int)(mode == kFprop ? K : N);
   if (mode == kWgrad) {
     g.n_qt = (int)(N / 128);
-    // 256 x 128 tiles where there are at least four per CU (16 experts of 2048 x 2048, 640 tokens:
-    // 82 us with 128 x 128, 69 with these; 32 experts of 4096 x 7168, 512 tokens: 1024 / 920); below,
-    // the small ones spread better (8 experts of 1024 x 256: 8.5 / 11.8)
-    const bool w256 = (int64_t)E * g.n_qt * ((K + 255) / 256) >= 4 * (int64_t)device_cu_count();
+    const bool w256 = wgrad_wide(E, M_cap, N, K, device_cu_count());
     g.rounds = M_cap <= 128 * (int64_t)E ? 1 : 4;
     g.n_pt = (int)(w256 ? (K + 255) / 256 : K / 128);
     const int64_t n = (int64_t)(E + 7) / 8 * 8 * g.n_qt * g.n_pt;  // whole periods of eight experts

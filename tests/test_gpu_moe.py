@@ -595,9 +595,9 @@ def test_layer_step_as_one_hip_graph(mode):
 @pytest.mark.parametrize("rows", [[2048, 128, 0, 256], [2000, 128, 0, 272], [512, 512, 512, 512]],
                          ids=["skewed", "skewed_align16", "uniform"])
 def test_wgrad_tile_schedules(rows):
-    """dW of four experts with 4096 x 4096 weights (16 x 16 tiles each).  When the largest
-    expert has more than twice the mean rows, the kernel splits every expert's tiles over
-    the 8 XCDs in equal 8 x 4-tile rectangles; otherwise it walks XCD blocks.  Both orders,
+    """dW of four experts with 4096 x 4096 weights (32 x 16 tiles of 128 x 256 each).  When the
+    largest expert has well over the mean rows, every XCD takes an eighth of every expert's
+    tiles; otherwise the XCDs take contiguous eighths of them all.  Both orders,
     with 128- and 16-row groups, against the oracle over the whole output; operands are
     random e4m3 codes with random power-of-two column-wise scales (rows outside the groups
     hold data too, which the kernel must not add)."""
@@ -713,8 +713,9 @@ def test_split_last_sweep_repeats_bit_for_bit(mode, rows, cols):
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
 
 
-# Token groups for wgrad: 128 x 128 tiles up to 832 tokens per expert, or 256 x 128 where those are
-# many, one or several tiles per workgroup; and 256 x 256 tiles in both XCD orders above.
+# Token groups for wgrad: 128 x 128 tiles where there are few, 256 x 128 where more, one or several
+# tiles per workgroup, both up to 1024 tokens per expert at most; and 256 x 256 tiles in both XCD
+# orders, and packed, above.
 TOKEN_CASES = {
     "short_one_tile_each": ([16, 128, 0, 48], 2048, 2176),
     "short_empty_first": ([0, 0, 272, 400], 1152, 640),
@@ -724,8 +725,15 @@ TOKEN_CASES = {
     # eleven experts (a period of eight and a part of one), an eighth of 108 tiles each per XCD
     "wide_shares": ([16, 1200, 0, 48, 16, 0, 272, 16, 528, 16, 32], 1152, 2944),
     "large_skewed": ([6000, 128, 0, 272], 4096, 4096),
+    # wide outputs (at least 3584 columns) and half a tile of them, at the small tiles' last sizes
     "large_uniform": ([1024, 912, 1040, 1024], 4096, 4096),
     "large_odd_columns": ([1024, 912, 0, 1040, 1024], 2048, 1408),
+    # two 256 x 128 tiles per CU; nine experts with between two and three of them, so 128 x 128
+    "one_round_wide": ([640, 528, 720, 672], 2048, 2048),
+    "second_round_short": ([256, 16, 0, 272, 128, 400, 32, 512, 144], 1024, 2048),
+    # 256 x 256 tiles in XCD blocks, and packed where the column tiles do not divide by four
+    "large_blocks": ([1152, 1040, 1168, 1248], 4096, 4096),
+    "large_packed": ([1152, 1408, 0, 1168, 1536], 2048, 1408),
 }
 
 

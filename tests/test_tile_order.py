@@ -119,7 +119,35 @@ FPROP, DGRAD, WGRAD = 0, 1, 2
     (DGRAD, 64, 64 * 16, 2048, 1408, 64),      # 56 / 40
     (FPROP, 32, 32 * 16, 7168, 2048, 64),      # 106 / 90
     (FPROP, 8, 8 * 96, 4096, 7168, 128),       # 80 / 57
+    (WGRAD, 32, 32 * 768, 7168, 2048, 0),      # 583 / 613
+    (WGRAD, 64, 64 * 766, 2816, 2048, 0),      # 474 / 510
+    (WGRAD, 64, 64 * 768, 7168, 2048, 0),      # 1158 / 1229
+    (WGRAD, 64, 64 * 768, 1024, 1024, 0),      # 96 / 99
+    (WGRAD, 8, 8 * 4096, 1024, 1280, 0),       # 56 / 70
+    (WGRAD, 8, 8 * 4096, 640, 1024, 128),      # 60 / 44
+    (WGRAD, 64, 64 * 384, 2816, 2048, 128),    # 383 / 344
+    (WGRAD, 64, 64 * 768, 2048, 1408, 128),    # 262 / 246
+    (WGRAD, 16, 16 * 768, 2816, 2048, 128),    # 131 / 122
+    (WGRAD, 32, 32 * 512, 7168, 2048, 128),    # 509 / 512
+    (WGRAD, 32, 32 * 1024, 4096, 7168, 128),   # 1358 / 1226
+    (WGRAD, 32, 32 * 1280, 4096, 7168, 0),     # 1509 / 1405, skewed 1443 / 1483
 ])
 def test_tile_shape_choice(host_lib, mode, E, M_cap, N, K, small):
     args = [ctypes.c_int64(v) for v in (M_cap, N, K, 256)]
     assert host_lib.tile_rule(mode, E, *args) == small
+
+
+@pytest.mark.parametrize("E,M_cap,N,K,wide", [
+    (4, 4 * 512, 2048, 2048, True),      # 128 x 128 tiles 28 us, 256 x 128 ones 23 (256 x 256: 25)
+    (16, 16 * 768, 1024, 1024, True),    # 35, 28 (31)
+    (15, 15 * 768, 1024, 2048, True),    # 56, 46 (48)
+    (12, 12 * 512, 1024, 2048, True),    # 37, 33
+    (32, 32 * 512, 4096, 7168, True),    # 1024, 920
+    (8, 8 * 512, 1024, 1024, False),     # 17, 19
+    (8, 8 * 256, 768, 2048, False),      # 18, 19
+    (9, 9 * 512, 1024, 2048, False),     # 27, 30
+    (10, 10 * 256, 1024, 2048, False)])  # 23, 25
+def test_wgrad_small_tile_choice(host_lib, E, M_cap, N, K, wide):
+    args = [ctypes.c_int64(v) for v in (M_cap, N, K, 256)]
+    assert host_lib.tile_rule(WGRAD, E, *args) == 128
+    assert host_lib.tile_rule_wide(E, *args) == wide
