@@ -81,7 +81,7 @@ template <int MODE> constexpr bool kStaggerK = (MODE == kFprop);
 
 __shared__ __attribute__((aligned(1024))) uint8_t g_st0[2 * kTileBytes], g_st1[2 * kTileBytes];  // [P | Q]
 __shared__ __attribute__((aligned(1024))) float g_sc[2][2 * kTP * kScaleBatch];  // [P rows x 4 | Q rows x 4]
-__shared__ int g_cum[1025];  // fprop/dgrad: cumulative 256-row tile counts per expert
+__shared__ int g_cum[1026];  // fprop/dgrad: cumulative 256-row tile counts per expert; behind them, packed or not
 __shared__ int g_off[1025];  // fprop/dgrad: expert row offsets
 
 template <int B> __device__ __forceinline__ uint8_t* stage_buf() {
@@ -729,6 +729,7 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
   T.wp = T.wave & 1;
   T.wq = T.wave >> 1;
   int n_qg;  // q tiles
+  bool packed = kPack;
   if (MODE != kWgrad) {
     // cumulative 256-row tile counts and row offsets per expert: one wave, 64 per pass
     if (tid < 64) {
@@ -751,10 +752,12 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
       if (tid == 0) {
         g_cum[0] = 0;
         g_off[0] = g.offsets[0];
+        if (kPack) g_cum[g.E + 1] = packing_saves(g.n_pt, carry, true);
       }
     }
     __syncthreads();
     n_qg = __builtin_amdgcn_readfirstlane(g_cum[g.E]);
+    if (kPack) packed = __builtin_amdgcn_readfirstlane(g_cum[g.E + 1]) != 0;
   } else {
     n_qg = g.E * g.n_qt;
   }
@@ -776,7 +779,7 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
     __syncthreads();
     use_share = __builtin_amdgcn_readfirstlane(g_cum[0]) != 0;
   }
-  const int n_blocks = order_blocks<kPack>(g, n_qg);
+  const int n_blocks = order_blocks(g.n_pt, n_qg, packed);
   int k = (int)(blockIdx.x / (8 * g.n_slots)) * kRoundsPerWg;
   TileInfo t;
   if (!next_tile<MODE, kPack>(g, g_cum, g_off, blockIdx.x, n_blocks, use_share, k, t)) return;
@@ -870,7 +873,7 @@ static hipError_t grouped_gemm_impl(GemmMode mode, const uint8_t* a, const SC* a
     const int64_t blocks_items = (blocks_of(g.n_pt, (int64_t)E * g.n_qt) + 7) / 8 * kPersistSlots;
     const int64_t share_items = (int64_t)E * g.share;
     grid = grid_items(share_items > blocks_items ? share_items : blocks_items, device_cu_count(), g.n_slots);
-    if (g.n_pt % kBP != 0)
+    if (g.n_pt % kBP != 0 && packing_saves(g.n_pt, E * g.n_qt, false))
       grouped_gemm_kernel<kWgrad, SC, true><<<grid, kThreads, 0, st>>>(g);
     else
       grouped_gemm_kernel<kWgrad, SC, false><<<grid, kThreads, 0, st>>>(g);

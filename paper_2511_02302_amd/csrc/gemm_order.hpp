@@ -70,19 +70,37 @@ __host__ __device__ __forceinline__ void wgrad_k_range(const GemmArgs& g, int e,
   t.k_hi = o1 > o0 ? o1 - (kb0 + (t.nk - 1) * kBK) : kBK;
 }
 
+// XCD blocks, or chunks of packed tiles, of a launch with n_qg q tiles.
+__host__ __device__ __forceinline__ int order_blocks(int n_pt, int n_qg, bool packed) {
+  return packed ? (n_qg * n_pt + kPersistSlots - 1) / kPersistSlots
+                : ((n_pt + kBP - 1) / kBP) * ((n_qg + kBQ - 1) / kBQ);
+}
+
+// Whether packing saves a sweep over the XCDs, or half of one where the last can be split.  Where it
+// does not, the blocks' tiles stay together and spread over more XCDs (us, packed / blocks: 16 experts
+// of 450 rows, 1536 x 4096, fprop 60 / 56; 8 of 700 rows, 1408 x 2048, 37 / 34; wgrad of 8 experts of
+// 1024 x 640, 1100 tokens 29 / 26).  Over 540 products of odd widths packing gains 8% on average, by
+// this rule 9%.
+__host__ __device__ __forceinline__ bool packing_saves(int n_pt, int n_qg, bool split) {
+  const int chunks = order_blocks(n_pt, n_qg, true), rest = chunks & 7;
+  const int halves = 2 * (chunks >> 3) + (rest == 0 ? 0 : split && rest <= 4 ? 1 : 2);
+  return halves < 2 * ((order_blocks(n_pt, n_qg, false) + 7) >> 3);
+}
+
 // Tile w_in of XCD block blk (kBQ x kBP tiles, p fastest).  False for tiles past the
 // edges.  fprop/dgrad: q tiles are 256-row tiles of the expert groups (cum / off:
 // cumulative tile counts and row offsets per expert, in LDS); n_qg: q tiles of the launch.
-// kPack (p tiles not a multiple of kBP): every third or so block would be cut by the p edge and
-// leave its XCD a part of the work, so the blocks' tiles are packed into chunks of 32 in block
+// kPack (p tiles not a multiple of kBP), packed: every third or so block would be cut by the p edge
+// and leave its XCD a part of the work, so the blocks' tiles are packed into chunks of 32 in block
 // order, and blk is a chunk; every chunk but the last is full.  64 experts of 1024 rows, 2048 x
 // 1408 (6 p tiles): dgrad 254 -> 220 us, wgrad 364 -> 310.  With whole blocks only, the longer
 // lookup between two tiles costs 1-2%, so those keep the short one.
 template <int MODE, bool kPack>
-__host__ __device__ __forceinline__ bool decode_tile(const GemmArgs& g, const int* cum, const int* off, int n_qg, int blk, int w_in,
+__host__ __device__ __forceinline__ bool decode_tile(const GemmArgs& g, const int* cum, const int* off, int n_qg, bool packed,
+                                                           int blk, int w_in,
                                                            TileInfo& t) {
   int qg, pt;  // global q-tile index, p tile
-  if constexpr (kPack) {
+  if (kPack && packed) {
     const int l = blk * kPersistSlots + w_in;
     if (l >= n_qg * g.n_pt) return false;
     const int row = l / (kBQ * g.n_pt), l_q = l - row * kBQ * g.n_pt;  // row of blocks
@@ -149,7 +167,8 @@ __host__ __device__ __forceinline__ void decode_share_tile(const GemmArgs& g, in
 }
 
 // Next tile of this workgroup from round k on, below round k_end (k advances past empty
-// edge tiles).  kPack, fprop / dgrad: where the last sweep over the XCDs has at most four chunks
+// edge tiles).  kPack: packed in wgrad (decided on the host), in fprop / dgrad by the entry behind
+// cum's last (the groups are known on the device only).  There, where the last sweep over the XCDs has at most four chunks
 // left, two XCDs take each, a half of every tile's rows (Sched<2>) each.
 template <int MODE, bool kPack>
 __host__ __device__ __forceinline__ bool next_tile(const GemmArgs& g, const int* cum, const int* off, int block_idx, int n_blocks,
@@ -161,6 +180,7 @@ __host__ __device__ __forceinline__ bool next_tile(const GemmArgs& g, const int*
   const int group = bid / group_size, in_group = bid - group * group_size;
   const int xcd = in_group & 7, slot = in_group >> 3, k_end = (group + 1) * kRoundsPerWg;
   const int n_qg = !kPack ? 0 : MODE == kWgrad ? g.E * g.n_qt : uniform(cum[g.E]);
+  const bool packed = kPack && (MODE == kWgrad || uniform(cum[g.E + 1]) != 0);
   for (; k < k_end; ++k) {
     const int i = k * n_slots + slot;
     if (MODE == kWgrad && use_share) {
@@ -169,9 +189,9 @@ __host__ __device__ __forceinline__ bool next_tile(const GemmArgs& g, const int*
       return true;
     }
     const int sweep = (i / kPersistSlots) * 8;
-    if (kPack && MODE != kWgrad && sweep == (n_blocks & ~7) && (n_blocks & 7) <= 4) {
+    if (packed && MODE != kWgrad && sweep == (n_blocks & ~7) && (n_blocks & 7) <= 4) {
       if (xcd >= 2 * (n_blocks & 7)) return false;
-      if (!decode_tile<MODE, kPack>(g, cum, off, n_qg, sweep + (xcd >> 1), i % kPersistSlots, t)) continue;
+      if (!decode_tile<MODE, kPack>(g, cum, off, n_qg, packed, sweep + (xcd >> 1), i % kPersistSlots, t)) continue;
       // q_end is the group's end, not the tile's: the odd half ends with the tile
       t.q0 += (xcd & 1) * (kTQ / 2);
       t.q_end = min(t.q_end, t.q0 + kTQ / 2);
@@ -180,16 +200,9 @@ __host__ __device__ __forceinline__ bool next_tile(const GemmArgs& g, const int*
     }
     const int blk = sweep + xcd;
     if (blk >= n_blocks) return false;
-    if (decode_tile<MODE, kPack>(g, cum, off, n_qg, blk, i % kPersistSlots, t)) return true;
+    if (decode_tile<MODE, kPack>(g, cum, off, n_qg, packed, blk, i % kPersistSlots, t)) return true;
   }
   return false;
-}
-
-// XCD blocks (kPack: chunks) of a launch with n_qg q tiles.
-template <bool kPack>
-__host__ __device__ __forceinline__ int order_blocks(const GemmArgs& g, int n_qg) {
-  return kPack ? (n_qg * g.n_pt + kPersistSlots - 1) / kPersistSlots
-               : ((g.n_pt + kBP - 1) / kBP) * ((n_qg + kBQ - 1) / kBQ);
 }
 
 // Grid: groups of n_slots workgroups per XCD (one per CU, the same number on each of the

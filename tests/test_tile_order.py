@@ -151,3 +151,22 @@ def test_wgrad_small_tile_choice(host_lib, E, M_cap, N, K, wide):
     args = [ctypes.c_int64(v) for v in (M_cap, N, K, 256)]
     assert host_lib.tile_rule(WGRAD, E, *args) == 128
     assert host_lib.tile_rule_wide(E, *args) == wide
+
+
+@pytest.mark.parametrize("rows,n_pt,packs", [
+    ([512] * 16, 6, False),        # six chunks, or eight blocks: one sweep either way (37 us packed, 34 in blocks)
+    ([448] * 16, 6, False),        # the same with halves of tiles (60, 56)
+    ([512] * 64, 11, True),        # 44 chunks, five and a half sweeps, or 48 blocks, six
+    ([1024] * 64, 6, True),        # 48 chunks, or 64 blocks
+    ([384] * 4 + [256] * 9, 10, True)])  # 17 q tiles: six chunks, or nine blocks
+def test_row_tiles_are_packed_where_it_saves_a_sweep(walk, rows, n_pt, packs):
+    _, t = walk(rows, n_pt)
+    spans = [len(set((t[t[:, 4] == b][:, 3] // 1024).tolist())) for b in set(t[:, 4].tolist())]
+    assert (max(spans) > 1) == packs  # a block's tiles lie in four columns of tiles
+
+
+@pytest.mark.parametrize("E,n_pt,n_qt,packs", [(8, 3, 4, False), (8, 6, 8, False), (64, 6, 8, True), (8, 9, 8, False)])
+def test_wgrad_tiles_are_packed_where_it_saves_a_sweep(walk, E, n_pt, n_qt, packs):
+    _, t = walk([1152] * E, n_pt, n_qt)
+    spans = [len(set((t[t[:, 4] == b][:, 3] // 1024).tolist())) for b in set(t[:, 4].tolist())]
+    assert (max(spans) > 1) == packs

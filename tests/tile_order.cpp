@@ -8,7 +8,8 @@ namespace {
 
 template <int MODE, bool kPack>
 long walk(ff8::GemmArgs g, const int* cum, const int* off, unsigned grid, int n_qg, int* out, long cap) {
-  const int n_blocks = ff8::order_blocks<kPack>(g, n_qg);
+  const bool packed = kPack && (MODE == ff8::kWgrad || cum[g.E + 1]);
+  const int n_blocks = ff8::order_blocks(g.n_pt, n_qg, packed);
   long n = 0;
   for (unsigned b = 0; b < grid; ++b) {
     int k = (int)(b / (8 * g.n_slots)) * ff8::kRoundsPerWg;
@@ -33,13 +34,14 @@ long walk(ff8::GemmArgs g, const int* cum, const int* off, unsigned grid, int n_
 extern "C" long tile_order_walk(int E, const int* offsets, int m_cap, int n_pt, int n_qt, int cus, int* out, long cap) {
   ff8::GemmArgs g{};
   g.E = E; g.offsets = offsets; g.n_pt = n_pt; g.n_qt = n_qt; g.Kdim = ff8::kBK; g.Nq = n_qt * ff8::kTQ;
-  static int cum[1025];
+  static int cum[1026];
   cum[0] = 0;
   for (int e = 0; e < E; ++e) cum[e + 1] = cum[e] + (offsets[e + 1] - offsets[e] + ff8::kTQ - 1) / ff8::kTQ;
   const int n_qg = n_qt ? E * n_qt : cum[E];
   const long bound = n_qt ? (long)E * n_qt : (m_cap + ff8::kTQ - 1) / ff8::kTQ + E;
   const unsigned grid = ff8::grid_blocks(ff8::blocks_of(n_pt, bound), cus, g.n_slots);
-  const bool pack = n_pt % ff8::kBP != 0;
+  cum[E + 1] = ff8::packing_saves(n_pt, n_qg, true);
+  const bool pack = n_pt % ff8::kBP != 0 && (!n_qt || ff8::packing_saves(n_pt, n_qg, false));
   if (n_qt) return pack ? walk<ff8::kWgrad, true>(g, cum, offsets, grid, n_qg, out, cap)
                         : walk<ff8::kWgrad, false>(g, cum, offsets, grid, n_qg, out, cap);
   return pack ? walk<ff8::kFprop, true>(g, cum, offsets, grid, n_qg, out, cap)
