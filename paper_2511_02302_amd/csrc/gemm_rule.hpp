@@ -5,6 +5,13 @@
 
 namespace ff8 {
 
+// Workgroups of the small tiles' kernel that one CU runs at once, of the per_cu that registers allow:
+// the tables of the experts' offsets take LDS, and above 360 experts only two of the three with TQ 64
+// fit.  Groups sized for three there leave a third of each waiting for a CU (16 rows, 512 x 1024: 512
+// experts, fprop 74 us, sized for two 71; 1024 experts 171 / 161).
+constexpr int kLdsPerCU = 160 * 1024;
+inline int small_per_cu(int per_cu, int lds) { return lds * per_cu <= kLdsPerCU ? per_cu : kLdsPerCU / lds; }
+
 // wgrad on the small tiles: 256 (K) x 128 (N) ones, or 128 x 128.  Two of either run on a CU.  Where at
 // most two of the first come to a CU, all run at once and need no second round as twice as many of the
 // others do, which pays from about four K stages on (us, 128 x 128 / 256 x 128: two per CU, 4 experts of

@@ -7,8 +7,8 @@
 // CU does these in turn (first loads, K loop, output) and multiplies padding rows; here
 //   * tiles are 128 (p) x TQ (q) with TQ = 64 or 128, so a group of few rows wastes little (wgrad,
 //     whose sizes do not depend on the routing, also 256 x 128: a quarter less DMA per product);
-//   * two or three workgroups share a CU (50 to 66 KB of LDS each), so one's loads and output
-//     run under the other's products;
+//   * two or three workgroups share a CU (51 to 70 KB of LDS each, and 4 or 8 bytes per expert), so
+//     one's loads and output run under the other's products;
 //   * each workgroup walks its tiles as one stream of K stages: the DMA runs two stages ahead of
 //     the products across tile boundaries, so no tile waits for its first loads.
 // A stage's fragments are all read into registers, a barrier then frees its buffer and the DMA
@@ -524,7 +524,7 @@ hipError_t run_small(GemmArgs g, int64_t tiles_max, hipStream_t st) {
   using S = Shape<MODE, TP, TQ, SC>;
   const int lds = S::kTabOff + (MODE == kWgrad ? g.E + 2 : 2 * (g.E + 1)) * (int)sizeof(int);
   const int64_t per_xcd = (tiles_max + 7) / 8;
-  int64_t slots = (int64_t)(device_cu_count() / 8) * S::kPerCU;
+  int64_t slots = (int64_t)(device_cu_count() / 8) * small_per_cu(S::kPerCU, lds);
   if (slots < 1) slots = 1;
   if (slots > per_xcd) slots = per_xcd;
   g.n_slots = (int)slots;

@@ -170,3 +170,11 @@ def test_wgrad_tiles_are_packed_where_it_saves_a_sweep(walk, E, n_pt, n_qt, pack
     _, t = walk([1152] * E, n_pt, n_qt)
     spans = [len(set((t[t[:, 4] == b][:, 3] // 1024).tolist())) for b in set(t[:, 4].tolist())]
     assert (max(spans) > 1) == packs
+
+
+@pytest.mark.parametrize("E,tq,per_cu", [(1, 64, 3), (360, 64, 3), (362, 64, 2), (1024, 64, 2), (1024, 128, 2)])
+def test_small_tile_workgroups_fit_a_cu(host_lib, E, tq, per_cu):
+    """Two stages of 128 + tq rows x 128 bytes, two scale batches, two tables of E + 1 entries."""
+    lds = 2 * (128 + tq) * 128 + 2 * (256 + 16 * tq) + 8 * (E + 1)
+    got = host_lib.tile_per_cu(3 if tq == 64 else 2, lds)
+    assert got == per_cu and got * lds <= 160 * 1024

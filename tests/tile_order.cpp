@@ -54,3 +54,4 @@ extern "C" int tile_rule(int mode, int E, int64_t M_cap, int64_t N, int64_t K, i
 extern "C" int tile_rule_wide(int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus) {
   return ff8::wgrad_wide(E, M_cap, N, K, cus);
 }
+extern "C" int tile_per_cu(int per_cu, int lds) { return ff8::small_per_cu(per_cu, lds); }
