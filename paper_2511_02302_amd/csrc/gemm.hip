@@ -278,7 +278,7 @@ struct Tile {
     } else if constexpr (kE8) {
       const uint8_t* B8 = reinterpret_cast<const uint8_t*>(&g_sc[b & 1][kQ ? kTP * kScaleBatch : 0]);
       if constexpr (MODE == kWgrad) {  // [K block][256 row bytes]
-        const int row = (kQ ? 32 * NB * wq : 128 * wp) + l31;
+        const int row = 128 * (kQ ? wq : wp) + l31;
 #pragma unroll
         for (int R = R0; R < R1; ++R)
 #pragma unroll
@@ -289,7 +289,7 @@ struct Tile {
       }
     } else if constexpr (MODE == kWgrad) {  // [K block][256 rows]
       const float* F = &g_sc[b & 1][kQ ? kTP * kScaleBatch : 0];
-      const int row = (kQ ? 32 * NB * wq : 128 * wp) + l31;
+      const int row = 128 * (kQ ? wq : wp) + l31;
 #pragma unroll
       for (int R = R0; R < R1; ++R)
 #pragma unroll
@@ -409,14 +409,13 @@ struct Tile {
       dma_slot<NB, B, S4, Sc::kSlots - Sc::kEarly + I>(ks_dma, ks_next);
       reads_of_slot<NB, 1 - B, 0, true, I>();
       if constexpr (NB == 2) {  // half the slots: two rows of P at a time, both of Q's
-        constexpr bool p_here = S4 == (kSpreadScales ? 1 : 3), q_here = S4 == 3;
-        const int bp = kSpreadScales ? (ks_next >> 2) + 1 : ks_next >> 2;
-        if constexpr (p_here && I == 4) read_scale_rows<NB, false, 0, 2>(bp, rsp);
-        if constexpr (p_here && I == 5) pack_scales<false, 0, 2>(rsp, np);
-        if constexpr (p_here && I == 5) read_scale_rows<NB, false, 2, 4>(bp, rsp);
-        if constexpr (p_here && I == 6) pack_scales<false, 2, 4>(rsp, np);
-        if constexpr (q_here && I == 6) read_scale_rows<NB, true, 0, 2>(ks_next >> 2, rsq);
-        if constexpr (q_here && I == 7) pack_scales<true, 0, 2>(rsq, nq);
+        static_assert(!kSpreadScales, "wgrad has no half tiles");
+        if constexpr (S4 == 3 && I == 4) read_scale_rows<NB, false, 0, 2>(ks_next >> 2, rsp);
+        if constexpr (S4 == 3 && I == 5) pack_scales<false, 0, 2>(rsp, np);
+        if constexpr (S4 == 3 && I == 5) read_scale_rows<NB, false, 2, 4>(ks_next >> 2, rsp);
+        if constexpr (S4 == 3 && I == 6) pack_scales<false, 2, 4>(rsp, np);
+        if constexpr (S4 == 3 && I == 6) read_scale_rows<NB, true, 0, 2>(ks_next >> 2, rsq);
+        if constexpr (S4 == 3 && I == 7) pack_scales<true, 0, 2>(rsq, nq);
       } else if constexpr (kSpreadScales) {
         if constexpr (S4 == 1 && I == 8) read_scale_rows<NB, false, 0, 2>((ks_next >> 2) + 1, rsp);
         if constexpr (S4 == 1 && I == 10) pack_scales<false, 0, 2>(rsp, np);
@@ -590,9 +589,9 @@ __device__ __forceinline__ void epilogue(Tile<MODE, SC>& T, const GemmArgs& g, c
   if (MODE == kWgrad) {
     // uniform base of this wave's 128 x 128 sub-tile, 32-bit lane offsets from it
     uint8_t* const dw = reinterpret_cast<uint8_t*>(
-        static_cast<float*>(g.out) + ((size_t)t.e * g.Nq + t.q0 + 32 * NB * wq) * g.Np + t.p0 + 128 * wp);
+        static_cast<float*>(g.out) + ((size_t)t.e * g.Nq + t.q0 + 128 * wq) * g.Np + t.p0 + 128 * wp);
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
+    for (int b = 0; b < 4; ++b) {
       // rows ql = l31 of 512 bytes (q = 32 b + ql); chunk c = p / 4 = 8a + 2gr + h
 #pragma unroll
       for (int a = 0; a < 4; ++a)
@@ -615,7 +614,7 @@ __device__ __forceinline__ void epilogue(Tile<MODE, SC>& T, const GemmArgs& g, c
 #pragma unroll
       for (int it = 0; it < 16; ++it) {
         const int qr = 32 * b + 2 * it + h;  // row within the wave's sub-tile
-        if (!p_ok || t.q0 + 32 * NB * wq + qr >= t.q_end) continue;
+        if (!p_ok || t.q0 + 128 * wq + qr >= t.q_end) continue;
         uint8_t* dst = dw + (uint32_t)(qr * g.Np + 4 * l31) * 4u;
         if (g.accumulate) {
           const u32x4 old = ld16(dst);
@@ -678,7 +677,9 @@ __device__ __forceinline__ void dma_stage(Tile<MODE, SC>& T, int ks) {
 // First-stage DMA of a tile: stage 0 into buffer 0, then the scale batch 0 (buffer 0).
 template <int MODE, typename SC>
 __device__ __forceinline__ void dma_first_stage(Tile<MODE, SC>& T) {
-  if (MODE != kWgrad && T.half) dma_stage<2, 0>(T, 0); else dma_stage<4, 0>(T, 0);
+  if constexpr (MODE == kWgrad) dma_stage<4, 0>(T, 0);
+  else if (T.half) dma_stage<2, 0>(T, 0);
+  else dma_stage<4, 0>(T, 0);
   T.template dma_scale_p<false>(0);
   T.template dma_scale_q<false>(0);
 }
@@ -794,9 +795,11 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
       for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) T.acc[a][b][v] = 0.0f;
-    const bool half = MODE != kWgrad && T.half;
+    [[maybe_unused]] const bool half = MODE != kWgrad && T.half;
     if (T.nk > 0) {
-      if (half) k_loop<2>(T); else k_loop<4>(T);
+      if constexpr (MODE == kWgrad) k_loop<4>(T);
+      else if (half) k_loop<2>(T);
+      else k_loop<4>(T);
     }
     lds_barrier();  // every wave is done with the stage buffers and the scale batches
     TileInfo tn;
@@ -807,7 +810,9 @@ __global__ __launch_bounds__(kThreads, 1) void grouped_gemm_kernel(GemmArgs g) {
       if (T.nk > 0) dma_first_stage<MODE, SC>(T);  // buffer 0 and scale batch 0, under the epilogue
     }
     if (!(MODE == kWgrad && t.nk == 0 && g.accumulate)) {
-      if (half) epilogue<2>(T, g, t); else epilogue<4>(T, g, t);
+      if constexpr (MODE == kWgrad) epilogue<4>(T, g, t);
+      else if (half) epilogue<2>(T, g, t);
+      else epilogue<4>(T, g, t);
     }
     if (!more) break;
     t = tn;

@@ -96,9 +96,8 @@ __host__ __device__ __forceinline__ bool packing_saves(int n_pt, int n_qg, bool 
 // 1408 (6 p tiles): dgrad 254 -> 220 us, wgrad 364 -> 310.  With whole blocks only, the longer
 // lookup between two tiles costs 1-2%, so those keep the short one.
 template <int MODE, bool kPack>
-__host__ __device__ __forceinline__ bool decode_tile(const GemmArgs& g, const int* cum, const int* off, int n_qg, bool packed,
-                                                           int blk, int w_in,
-                                                           TileInfo& t) {
+__host__ __device__ __forceinline__ bool decode_tile(const GemmArgs& g, const int* cum, const int* off, int n_qg,
+                                                     bool packed, int blk, int w_in, TileInfo& t) {
   int qg, pt;  // global q-tile index, p tile
   if (kPack && packed) {
     const int l = blk * kPersistSlots + w_in;
@@ -168,11 +167,13 @@ __host__ __device__ __forceinline__ void decode_share_tile(const GemmArgs& g, in
 
 // Next tile of this workgroup from round k on, below round k_end (k advances past empty
 // edge tiles).  kPack: packed in wgrad (decided on the host), in fprop / dgrad by the entry behind
-// cum's last (the groups are known on the device only).  There, where the last sweep over the XCDs has at most four chunks
-// left, two XCDs take each, a half of every tile's rows (Sched<2>) each.
+// cum's last (the groups are known on the device only).  There, where the last sweep over the XCDs
+// has at most four chunks left, two XCDs take each, a half of every tile's rows (Sched<2>) each:
+// fprop of 2816 x 2048, 64 experts, 4096 tokens x 6 (44 chunks) 183 -> 172 us; 16 experts, 2048
+// tokens x 2 (11 or 12 chunks) 57 -> 53.
 template <int MODE, bool kPack>
-__host__ __device__ __forceinline__ bool next_tile(const GemmArgs& g, const int* cum, const int* off, int block_idx, int n_blocks,
-                                                         bool use_share, int& k, TileInfo& t) {
+__host__ __device__ __forceinline__ bool next_tile(const GemmArgs& g, const int* cum, const int* off, int block_idx,
+                                                   int n_blocks, bool use_share, int& k, TileInfo& t) {
   // fprop / dgrad: from the opaque block index, so that none of it stays in registers across the
   // K loop (dgrad spilled two; wgrad has room, and is 1% slower with this)
   const int bid = MODE != kWgrad ? opaque_uniform(block_idx) : block_idx;
