@@ -31,7 +31,7 @@ HBM_PEAK_GBS = 8000.0         # MI355X HBM3E
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_expert_layer_dsv3.md")
 CSRC = os.path.join(ROOT, "paper_2511_02302_amd", "csrc")
 # Kernel source each stage runs; the measured traffic of a stage is only reported while
-# the hash of its source (and the shared device header) still matches the measurement.
+# the hash of its source files (source_files) still matches the measurement.
 STAGE_SOURCE = {"F0_weight_quant": "quant.hip", "F1_permute_quant": "permute.hip", "F2_fc1_fprop": "gemm.hip",
                 "F3_swiglu_quant": "swiglu.hip", "F4_fc2_fprop": "gemm.hip", "F5_unpermute": "permute.hip",
                 "B1_permute_quant_dy": "permute.hip", "B2_fc2_dgrad": "gemm.hip", "B3_swiglu_bwd_quant": "swiglu.hip",
@@ -551,11 +551,17 @@ def cast_ops(torch, reps=20):
     return out
 
 
+def source_files(stage):
+    """What decides the kernel a stage launches and what it does (not the launchers' declarations)."""
+    src = STAGE_SOURCE[stage]
+    gemm = ("gemm_small.hip", "gemm_order.hpp", "gemm_rule.hpp", "gemm_shared.hpp") if src == "gemm.hip" else ()
+    return (src, "ff8_device.hpp") + gemm
+
+
 def source_hash(stage):
     import hashlib
     h = hashlib.sha256()
-    src = STAGE_SOURCE[stage]
-    for f in (src, "ff8_device.hpp") + (("gemm_shared.hpp",) if src == "gemm.hip" else ()):
+    for f in source_files(stage):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
