@@ -237,9 +237,11 @@ __global__ __launch_bounds__(kChunk) void route_assign_scan_kernel(const int32_t
   __syncthreads();
   if (chunk == 0)
     for (int e = tid; e <= E; e += kChunk) offsets[e] = offs[e];
-  // padding rows of the groups (fewer than 128 each): src_row = -1, wave by wave
-  for (int e = chunk * 4 + (tid >> 6); e < E; e += gridDim.x * 4)
-    for (int r = offs[e] + total[e] + (tid & 63); r < offs[e + 1]; r += 64) src_row[r] = -1;
+  // padding rows of the groups (fewer than 128 each): src_row = -1, sixteen lanes per group (a whole
+  // wave for each, one after the other, was most of a launch with many experts and few chunks: 7 tokens
+  // over 1024 experts, 128 columns with 16-row padding, 29.7 -> 15.6 us)
+  for (int e = chunk * 16 + (tid >> 4); e < E; e += gridDim.x * 16)
+    for (int r = offs[e] + total[e] + (tid & 15); r < offs[e + 1]; r += 16) src_row[r] = -1;
   for (int e = tid; e < E; e += kChunk) base[e] += offs[e];
   __syncthreads();
   assign_rows(idx, chunk, T, k, E, base, mask, row_map, src_row);

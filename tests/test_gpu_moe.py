@@ -762,7 +762,8 @@ def test_token_tile_shapes(case):
 
 
 @pytest.mark.parametrize("T,k,E,align", [(1024, 4, 600, 16), (1, 1, 1, 128), (256, 2, 256, 128), (2100, 2, 300, 16),
-                                         (2049, 2, 8, 128), (4200, 1, 1000, 16), (4300, 2, 512, 128)])
+                                         (2049, 2, 8, 128), (4200, 1, 1000, 16), (4300, 2, 512, 128),
+                                         (7, 2, 1024, 16), (300, 1, 1024, 128), (4200, 1, 1000, 128)])
 def test_routing_launches(T, k, E, align):
     """Routing maps where they come from one, two or three launches: the pairs counted by every
     chunk (up to 4096), the chunks' counts summed by every chunk, and the separate scan; more
