@@ -554,8 +554,9 @@ def cast_ops(torch, reps=20):
 def source_files(stage):
     """What decides the kernel a stage launches and what it does (not the launchers' declarations)."""
     src = STAGE_SOURCE[stage]
-    gemm = ("gemm_small.hip", "gemm_order.hpp", "gemm_rule.hpp", "gemm_shared.hpp") if src == "gemm.hip" else ()
-    return (src, "ff8_device.hpp") + gemm
+    more = {"gemm.hip": ("gemm_small.hip", "gemm_order.hpp", "gemm_rule.hpp", "gemm_shared.hpp"),
+            "permute.hip": ("route_rule.hpp",)}
+    return (src, "ff8_device.hpp") + more.get(src, ())
 
 
 def source_hash(stage):

@@ -26,6 +26,7 @@
 
 #include "ff8_device.hpp"
 #include "ff8_launch.hpp"
+#include "route_rule.hpp"
 
 namespace ff8 {
 
@@ -486,19 +487,14 @@ hipError_t launch_route(const int32_t* topk_idx, int64_t T, int k, int E, int al
   (void)M_cap;
   const int64_t nc = n_chunks_of(T);
   int32_t* counts = static_cast<int32_t*>(workspace);
-  // Launches of the routing, by what a chunk's workgroup would have to sum by itself (us with the
-  // permute of 128 columns behind them, one / two / three launches): all the pairs, up to 4096 (7
-  // tokens x 6: 10.7 / 12.6 / 13.9; 1024 x 2: 9.2 / 10.5 / 13.1; 1024 x 8: 16.8 / 15.1 / 17.7);
-  // all the counts, up to 8192 (16384 tokens, 64 experts: 25.3 with two launches, 28.8 with three;
-  // 256 experts, 16384 counts: 36.1 / 34.1), and up to 32768 above 512 experts, where the scan's
-  // threads walk their chunks one by one (8192 tokens, 1024 experts: 50.2 / 70.4).
   const unsigned grid = (unsigned)(nc > 0 ? nc : 1);
-  if (T * k <= 4096) {
+  const int launches = route_launches(T, k, E, align);
+  if (launches == 1) {
     route_assign_scan_kernel<true><<<grid, kChunk, 0, st>>>(topk_idx, T, k, E, align, nullptr, nc, row_map, offsets, src_row);
     return hipGetLastError();
   }
   if (nc > 0) route_count_kernel<<<(unsigned)nc, kChunk, 0, st>>>(topk_idx, T, k, E, counts);
-  if (nc * E <= 8192 || (E > 512 && nc * E <= 32768)) {
+  if (launches == 2) {
     route_assign_scan_kernel<false><<<grid, kChunk, 0, st>>>(topk_idx, T, k, E, align, counts, nc, row_map, offsets, src_row);
     return hipGetLastError();
   }

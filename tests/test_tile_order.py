@@ -1,9 +1,10 @@
-"""Which tiles the grouped GEMMs run, and in which order (CPU only; tile_order.cpp compiles the
-library's own functions for the host).
+"""Which tiles the grouped GEMMs run, in which order, and the launches of a routing (CPU only;
+tile_order.cpp compiles the library's own functions for the host).
 
 The 256 x 256 tiles cover every output row and column exactly once: two workgroups that store the
 same rows race, and fprop's K rotation follows the XCD block, so the bits that stay would depend on
-timing.  The choice between them and the small tiles is the faster one at measured sizes.
+timing.  The choice between them and the small tiles is the faster one at measured sizes, and so is
+the number of launches that a routing takes.
 """
 
 import ctypes
@@ -178,3 +179,14 @@ def test_small_tile_workgroups_fit_a_cu(host_lib, E, tq, per_cu):
     lds = 2 * (128 + tq) * 128 + 2 * (256 + 16 * tq) + 8 * (E + 1)
     got = host_lib.tile_per_cu(3 if tq == 64 else 2, lds)
     assert got == per_cu and got * lds <= 160 * 1024
+
+
+@pytest.mark.parametrize("T,k,E,align,launches", [
+    (7, 1, 1024, 16, 1), (4096, 1, 1024, 128, 1), (512, 8, 8, 128, 1),
+    (513, 8, 8, 128, 2), (16384, 8, 64, 128, 2), (4096, 8, 512, 16, 2),
+    (8192, 1, 1024, 128, 2),            # two launches 50 us, three 94
+    (8192, 1, 1024, 16, 3),             # 48, 35
+    (8192, 2, 768, 16, 3),              # 41, 34
+    (8192, 2, 512, 16, 3), (16384, 8, 256, 128, 3)])
+def test_routing_launch_count(host_lib, T, k, E, align, launches):
+    assert host_lib.route_launch_count(ctypes.c_int64(T), k, E, align) == launches

@@ -1,8 +1,9 @@
-// Host side of the grouped GEMMs' tiles, for test_tile_order.py: the choice of the tile shape, and a
-// walk of the 256 x 256 tiles' order, every tile of every workgroup of a launch, as the kernel's own
+// Host side of the grouped GEMMs' tiles and of the routing's launches, for test_tile_order.py: the
+// choice of the tile shape and of the launches, and a walk of the 256 x 256 tiles' order, every tile of every workgroup of a launch, as the kernel's own
 // functions give them.
 #include "gemm_order.hpp"
 #include "gemm_rule.hpp"
+#include "route_rule.hpp"
 
 namespace {
 
@@ -55,3 +56,4 @@ extern "C" int tile_rule_wide(int E, int64_t M_cap, int64_t N, int64_t K, int64_
   return ff8::wgrad_wide(E, M_cap, N, K, cus);
 }
 extern "C" int tile_per_cu(int per_cu, int lds) { return ff8::small_per_cu(per_cu, lds); }
+extern "C" int route_launch_count(int64_t T, int k, int E, int align) { return ff8::route_launches(T, k, E, align); }
