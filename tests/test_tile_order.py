@@ -113,6 +113,11 @@ FPROP, DGRAD, WGRAD = 0, 1, 2
     (FPROP, 8, 8 * 192, 4096, 7168, 128),      # 96 / 84
     (FPROP, 8, 8 * 256, 1024, 1024, 64),       # 24 / 12
     (DGRAD, 16, 16 * 192, 6912, 1024, 64),     # 88 / 52
+    # up to 256 rows per group: at least one tile per expert
+    (DGRAD, 64, 64 * 128, 2048, 1408, 128),    # 61 / 50
+    (DGRAD, 64, 64 * 160, 2048, 1408, 128),    # 61 / 50, skewed 29 / 21
+    (FPROP, 64, 64 * 136, 2816, 2048, 128),    # 92 / 89
+    (FPROP, 30, 30 * 128, 7040, 256, 128),     # a step with these: 376 us / 364
     # a few rows per group
     (DGRAD, 8, 8 * 16, 4096, 7168, 0),         # 53 / 59
     (DGRAD, 32, 32 * 48, 4096, 7168, 0),       # 205 / 205; skewed 104 / 125
