@@ -75,10 +75,10 @@ inline bool wgrad_small(int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus)
 //    here: none if the groups are whole tiles, so the small ones have to win on that count too (it
 //    can be a whole round: 8 experts of 4096 x 7168, fprop of 512 rows: 97 / 148; 16 of 2048 x 2048:
 //    39 / 52).  But experts share no tile: with up to 256 rows each they are at least as many (64
-//    experts of 2048 x 1408, dgrad of 128 rows: 61 / 50).  16 experts of 2048 x 2048, fprop: 192 rows 37 / 31, 256 40 / 32, 384 34 / 40; 8
-//    of 4096 x 7168: 192 rows 96 / 84; dgrad: 192 rows 67 / 105.  TQ 64 when even 128 x 128 tiles do not
-//    reach every CU, or reach it once for a few stages (8 experts of 1024 x 1024, 256 rows: 14.0 with
-//    TQ 128, 12.1 with 64).
+//    experts of 2048 x 1408, dgrad of 128 rows: 61 / 50).  16 experts of 2048 x 2048, fprop: 192 rows
+//    37 / 31, 256 40 / 32, 384 34 / 40; 8 of 4096 x 7168: 192 rows 96 / 84; dgrad: 192 rows 67 / 105.  TQ
+//    64 when even 128 x 128 tiles do not reach every CU, or reach it once for a few stages (8 experts of
+//    1024 x 1024, 256 rows: 14.0 with TQ 128, 12.1 with 64).
 //  * wgrad: see wgrad_small.
 inline int small_gemm_tile(GemmMode mode, int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus) {
   if (mode == kWgrad) return wgrad_small(E, M_cap, N, K, cus) ? 128 : 0;
@@ -95,11 +95,11 @@ inline int small_gemm_tile(GemmMode mode, int E, int64_t M_cap, int64_t N, int64
   // q tiles: the rows' own, with a share of one per expert for the groups' last, partial tiles and
   // without; at least one per expert
   const int64_t n_pt = (Np + 255) / 256;
-  const int64_t whole = std::max<int64_t>((M_cap + 255) / 256, E) * n_pt;
-  const int64_t large = std::max<int64_t>(M_cap / 256 + (E + 7) / 8, E) * n_pt;
+  const int64_t whole = (M_cap + 255) / 256, parts = M_cap / 256 + (E + 7) / 8;
+  auto beats = [&](int64_t t, int64_t q) { return t < t_large(std::max<int64_t>(q, E) * n_pt); };
   const int64_t small = (M_cap / 128 + (E + 7) / 8) * (Np / 128);
   const int64_t t_small = small * (f ? 142 : 155) * nk / (2 * cus) + 700;
-  if (large > 3 * cus || t_small >= t_large(large) || t_small >= t_large(whole)) return 0;
+  if (parts * n_pt > 3 * cus || !beats(t_small, parts) || !beats(t_small, whole)) return 0;
   return small < cus || (small < 2 * cus && nk <= 8) ? 64 : 128;
 }
 
