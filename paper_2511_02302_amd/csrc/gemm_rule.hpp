@@ -1,8 +1,6 @@
 // Which tiles a grouped product takes, by its sizes: host code only.
 #pragma once
 
-#include <algorithm>
-
 #include "gemm_shared.hpp"
 
 namespace ff8 {
@@ -74,11 +72,13 @@ inline bool wgrad_small(int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus)
 //    of a round of 512 small ones.  How many tiles the groups' last, partial ones add is not known
 //    here: none if the groups are whole tiles, so the small ones have to win on that count too (it
 //    can be a whole round: 8 experts of 4096 x 7168, fprop of 512 rows: 97 / 148; 16 of 2048 x 2048:
-//    39 / 52).  But experts share no tile: with up to 256 rows each they are at least as many (64
-//    experts of 2048 x 1408, dgrad of 128 rows: 61 / 50).  16 experts of 2048 x 2048, fprop: 192 rows
-//    37 / 31, 256 40 / 32, 384 34 / 40; 8 of 4096 x 7168: 192 rows 96 / 84; dgrad: 192 rows 67 / 105.  TQ
-//    64 when even 128 x 128 tiles do not reach every CU, or reach it once for a few stages (8 experts of
-//    1024 x 1024, 256 rows: 14.0 with TQ 128, 12.1 with 64).
+//    39 / 52).  But experts share no tile: with up to 256 rows each they are as many as the experts
+//    that have any (64 experts of 2048 x 1408, dgrad of 128 rows: 61 / 50), and the small ones then
+//    only have to win by a sixteenth on that count (closer, groups of just over 128 rows cost them more:
+//    32 experts of 7168 x 2048, fprop of 128 rows on average, 121 / 138).  16 experts of 2048 x 2048,
+//    fprop: 192 rows 37 / 31, 256 40 / 32, 384 34 / 40; 8 of 4096 x 7168: 192 rows 96 / 84; dgrad: 192
+//    rows 67 / 105.  TQ 64 when even 128 x 128 tiles do not reach every CU, or reach it once for a few
+//    stages (8 experts of 1024 x 1024, 256 rows: 14.0 with TQ 128, 12.1 with 64).
 //  * wgrad: see wgrad_small.
 inline int small_gemm_tile(GemmMode mode, int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus) {
   if (mode == kWgrad) return wgrad_small(E, M_cap, N, K, cus) ? 128 : 0;
@@ -92,11 +92,12 @@ inline int small_gemm_tile(GemmMode mode, int E, int64_t M_cap, int64_t N, int64
     const int64_t small = E * Np * Kd / rate + 200, large = t_large(E * ((Np + 255) / 256));
     return (f ? small : small + small / 16) < large ? tq : 0;
   }
-  // q tiles: the rows' own, with a share of one per expert for the groups' last, partial tiles and
-  // without; at least one per expert
+  // q tiles: the rows' own, with a share of one per expert for the groups' last, partial tiles and without
   const int64_t n_pt = (Np + 255) / 256;
   const int64_t whole = (M_cap + 255) / 256, parts = M_cap / 256 + (E + 7) / 8;
-  auto beats = [&](int64_t t, int64_t q) { return t < t_large(std::max<int64_t>(q, E) * n_pt); };
+  auto beats = [&](int64_t t, int64_t q) {
+    return t < t_large(q * n_pt) || (q < E && t + t / 16 < t_large(E * n_pt));
+  };
   const int64_t small = (M_cap / 128 + (E + 7) / 8) * (Np / 128);
   const int64_t t_small = small * (f ? 142 : 155) * nk / (2 * cus) + 700;
   if (parts * n_pt > 3 * cus || !beats(t_small, parts) || !beats(t_small, whole)) return 0;

@@ -116,7 +116,8 @@ FPROP, DGRAD, WGRAD = 0, 1, 2
     # up to 256 rows per group: at least one tile per expert
     (DGRAD, 64, 64 * 128, 2048, 1408, 128),    # 61 / 50
     (DGRAD, 64, 64 * 160, 2048, 1408, 128),    # 61 / 50, skewed 29 / 21
-    (FPROP, 64, 64 * 136, 2816, 2048, 128),    # 92 / 89
+    (DGRAD, 32, 32 * 128, 4096, 7168, 0),      # 221 / 237
+    (FPROP, 32, 32 * 144, 7168, 2048, 0),      # 121 / 138
     (FPROP, 30, 30 * 128, 7040, 256, 128),     # a step with these: 376 us / 364
     # a few rows per group
     (DGRAD, 8, 8 * 16, 4096, 7168, 0),         # 53 / 59
