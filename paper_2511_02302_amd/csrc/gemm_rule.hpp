@@ -61,46 +61,46 @@ inline bool wgrad_small(int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus)
 //    weights, the large tiles in whole rounds of one tile per CU (1.45 us per K stage, 3.5 us per
 //    round and 4.5 us once), these at 5.6 MB/us (fprop) or 4.75 (dgrad, whose loads are 128-byte
 //    runs of the weight's rows) with TQ 64 and 4.7 or 4.25 with TQ 128, which groups above 64 rows
-//    need.  The cheaper of the two, for dgrad by a sixteenth (where they come closer the small tiles
-//    gain nothing, and a skewed routing costs them more: 32 experts of 4096 x 7168, 256 tokens x 4,
-//    Zipf(1.2): 104 / 125): 16 rows, 32 experts of 4096 x 7168: fprop 174 / 166, dgrad 205 / 205; 8 of
-//    them: 74 / 47, 53 / 59; 32 of 7168 x 2048: 106 / 90, 95 / 101; 64 of 2816 x 2048: 85 / 75, 77 / 86;
-//    of 2048 x 1408: 46 / 40, 56 / 40; 64 rows: 183 / 175, 213 / 214; 79 / 49, 56 / 59; 109 / 94, 95 /
-//    104; 87 / 79, 79 / 88; 48 / 42, 58 / 42.
+//    need.  The cheaper of the two: 16 rows, 32 experts of 4096 x 7168: fprop 174 / 166, dgrad 205 /
+//    205; 8 of them: 74 / 47, 53 / 59; 32 of 7168 x 2048: 106 / 90, 95 / 101; 64 of 2816 x 2048: 85 / 75,
+//    77 / 86; of 2048 x 1408: 46 / 40, 56 / 40; 64 rows: 183 / 175, 213 / 214; 79 / 49, 56 / 59; 109 /
+//    94, 95 / 104; 87 / 79, 79 / 88; 48 / 42, 58 / 42.  With tokens for a few of the experts only, the
+//    small ones do less where a large tile's K loop is as long (28 of 4096 x 2048, 58 tokens, dgrad 43 /
+//    26); where a few experts hold most tokens, they read those weights once per 64 rows (32 of 4096 x
+//    7168, 256 tokens x 4, Zipf(1.2): 97 / 107, 104 / 125).
 //  * fprop, dgrad on grids of at most three 256 x 256 tiles per CU, where whole rounds of such
 //    tiles leave CUs idle: the same model of the large tiles against 1.42 us (dgrad 1.55) per stage
-//    of a round of 512 small ones.  How many tiles the groups' last, partial ones add is not known
-//    here: none if the groups are whole tiles, so the small ones have to win on that count too (it
-//    can be a whole round: 8 experts of 4096 x 7168, fprop of 512 rows: 97 / 148; 16 of 2048 x 2048:
-//    39 / 52).  But experts share no tile: with up to 256 rows each they are as many as the experts
-//    that have any (64 experts of 2048 x 1408, dgrad of 128 rows: 61 / 50), and the small ones then
-//    only have to win by a sixteenth on that count (closer, groups of just over 128 rows cost them more:
-//    32 experts of 7168 x 2048, fprop of 128 rows on average, 121 / 138).  16 experts of 2048 x 2048,
-//    fprop: 192 rows 37 / 31, 256 40 / 32, 384 34 / 40; 8 of 4096 x 7168: 192 rows 96 / 84; dgrad: 192
-//    rows 67 / 105.  TQ 64 when even 128 x 128 tiles do not reach every CU, or reach it once for a few
-//    stages (8 experts of 1024 x 1024, 256 rows: 14.0 with TQ 128, 12.1 with 64).
+//    of a round of 512 small ones.  16 experts of 2048 x 2048, fprop: 192 rows 37 / 31, 256 40 / 32, 384
+//    34 / 40; 8 of 4096 x 7168: 192 rows 96 / 84; dgrad: 192 rows 67 / 105.  The groups' last, partial
+//    tiles are an eighth of one per expert on average, but none where M_cap is whole tiles for every
+//    expert, and then the share can be a round too many (512 rows each, fprop: 8 experts of 4096 x 7168
+//    97 / 148, 16 of 2048 x 2048 39 / 52).  Experts share no tile, so up to 256 rows there are as many
+//    as experts that have any; on that count the small ones, whose own is then low as well, have to
+//    win by an eighth (dgrad a quarter): 64 experts of 2048 x 1408, dgrad of 128 rows 61 / 50; 49 of
+//    1792 x 3456, 9 tokens, fprop 39 / 26; closer, 32 of 7168 x 2048, fprop of 128 rows on average 121 /
+//    138, 30 of 1024 x 5120, one token x 7, dgrad 21 / 25.  TQ 64 when even 128 x 128 tiles do not reach
+//    every CU, or reach it once for a few stages (8 experts of 1024 x 1024, 256 rows: 14.0 with TQ 128,
+//    12.1 with 64).
 //  * wgrad: see wgrad_small.
 inline int small_gemm_tile(GemmMode mode, int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus) {
   if (mode == kWgrad) return wgrad_small(E, M_cap, N, K, cus) ? 128 : 0;
   const int64_t Np = mode == kFprop ? N : K, Kd = mode == kFprop ? K : N, nk = Kd / kBK;
   const bool f = mode == kFprop;
-  // hundredths of a microsecond for n tiles of 256 x 256
-  auto t_large = [&](int64_t n) { return (n + cus - 1) / cus * (145 * nk + 350) + 450; };
+  const int64_t n_pt = (Np + 255) / 256;
+  // hundredths of a microsecond for q tiles of 256 rows
+  auto t_large = [&](int64_t q) { return (q * n_pt + cus - 1) / cus * (145 * nk + 350) + 450; };
   if (M_cap <= 96 * (int64_t)E) {
     const int tq = M_cap <= 64 * (int64_t)E ? 64 : 128;
     const int64_t rate = tq == 64 ? (f ? 56000 : 47500) : (f ? 47000 : 42500);  // bytes per 0.01 us
-    const int64_t small = E * Np * Kd / rate + 200, large = t_large(E * ((Np + 255) / 256));
-    return (f ? small : small + small / 16) < large ? tq : 0;
+    return E * Np * Kd / rate + 200 < t_large(E) ? tq : 0;
   }
-  // q tiles: the rows' own, with a share of one per expert for the groups' last, partial tiles and without
-  const int64_t n_pt = (Np + 255) / 256;
-  const int64_t whole = (M_cap + 255) / 256, parts = M_cap / 256 + (E + 7) / 8;
-  auto beats = [&](int64_t t, int64_t q) {
-    return t < t_large(q * n_pt) || (q < E && t + t / 16 < t_large(E * n_pt));
-  };
+  const int64_t q_tiles = M_cap / 256 + (E + 7) / 8;
   const int64_t small = (M_cap / 128 + (E + 7) / 8) * (Np / 128);
   const int64_t t_small = small * (f ? 142 : 155) * nk / (2 * cus) + 700;
-  if (parts * n_pt > 3 * cus || !beats(t_small, parts) || !beats(t_small, whole)) return 0;
+  const bool whole = M_cap % (256 * (int64_t)E) == 0;
+  const bool wins = t_small < t_large(q_tiles) && !(whole && t_small >= t_large(M_cap / 256));
+  const bool wins_by_experts = q_tiles < E && t_small + t_small / (f ? 8 : 4) < t_large(E);
+  if (q_tiles * n_pt > 3 * cus || !(wins || wins_by_experts)) return 0;
   return small < cus || (small < 2 * cus && nk <= 8) ? 64 : 128;
 }
 

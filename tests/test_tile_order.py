@@ -119,9 +119,15 @@ FPROP, DGRAD, WGRAD = 0, 1, 2
     (DGRAD, 32, 32 * 128, 4096, 7168, 0),      # 221 / 237
     (FPROP, 32, 32 * 144, 7168, 2048, 0),      # 121 / 138
     (FPROP, 30, 30 * 128, 7040, 256, 128),     # a step with these: 376 us / 364
+    (FPROP, 60, 60 * 128, 2048, 3072, 128),    # 2 tokens x 6: 40 / 28
+    (FPROP, 49, 49 * 128, 1792, 3456, 128),    # 9 tokens: 39 / 26
+    (FPROP, 63, 15872, 1024, 1024, 128),       # 47 / 38
+    (FPROP, 27, 4864, 3328, 4096, 128),        # 100 / 90
+    (DGRAD, 30, 30 * 128, 1024, 5120, 0),      # one token x 7: 21 / 25
+    (DGRAD, 47, 6272, 1024, 5120, 0),          # 67 tokens x 3, skewed: 21 / 25
     # a few rows per group
-    (DGRAD, 8, 8 * 16, 4096, 7168, 0),         # 53 / 59
-    (DGRAD, 32, 32 * 48, 4096, 7168, 0),       # 205 / 205; skewed 104 / 125
+    (DGRAD, 28, 28 * 18, 4096, 2048, 64),      # 58 tokens: 43 / 26
+    (DGRAD, 48, 48 * 16, 2560, 1280, 64),      # 4 tokens x 7: 34 / 21
     (DGRAD, 32, 32 * 16, 7168, 2048, 0),       # 95 / 101
     (DGRAD, 64, 64 * 16, 2048, 1408, 64),      # 56 / 40
     (FPROP, 32, 32 * 16, 7168, 2048, 64),      # 106 / 90
