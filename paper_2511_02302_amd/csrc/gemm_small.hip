@@ -549,7 +549,7 @@ hipError_t grouped_gemm_small_impl(GemmMode mode, int tq, const uint8_t* a, cons
   g.Kdim = (int)(mode == kFprop ? K : N);
   if (mode == kWgrad) {
     g.n_qt = (int)(N / 128);
-    const bool w256 = wgrad_wide(E, M_cap, N, K, device_cu_count());
+    const bool w256 = wgrad_wide(E, N, K, device_cu_count());
     g.rounds = M_cap <= 128 * (int64_t)E ? 1 : 4;
     g.n_pt = (int)(w256 ? (K + 255) / 256 : K / 128);
     const int64_t n = (int64_t)(E + 7) / 8 * 8 * g.n_qt * g.n_pt;  // whole periods of eight experts

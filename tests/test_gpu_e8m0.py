@@ -149,7 +149,7 @@ def test_layer_step_e8m0_equals_f32(case):
                                                     ([512, 272], 1024, 1024), ([1024, 784], 22528, 512))],
     ("wgrad", [16, 128, 0, 48], 512, 1152), ("wgrad", [640, 16, 528, 0], 1920, 1024),
     ("wgrad", [640, 16, 528, 0], 4224, 2176),
-    ("wgrad", [1024, 912, 1040, 1024], 2048, 4096), ("wgrad", [1152, 912, 1168, 1040], 2048, 4096)])
+    ("wgrad", [1024, 912, 1040, 1024], 2048, 4096)])
 def test_tile_shapes_e8m0_equal_f32(mode, rows, cols, depth):
     """The same bytes and bits from float32 scales and from their UE8M0 bytes."""
     E, rng = len(rows), np.random.default_rng(sum(rows) + cols)

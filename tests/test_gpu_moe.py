@@ -714,8 +714,8 @@ def test_split_last_sweep_repeats_bit_for_bit(mode, rows, cols):
 
 
 # Token groups for wgrad: 128 x 128 tiles where there are few, 256 x 128 where more, one or several
-# tiles per workgroup, both up to 1024 tokens per expert at most; and 256 x 256 tiles in both XCD
-# orders, and packed, above.
+# tiles per workgroup, both up to 832 tokens per expert; and 256 x 256 tiles in both XCD orders, and
+# packed, above.
 TOKEN_CASES = {
     "short_one_tile_each": ([16, 128, 0, 48], 2048, 2176),
     "short_empty_first": ([0, 0, 272, 400], 1152, 640),
@@ -725,14 +725,14 @@ TOKEN_CASES = {
     # eleven experts (a period of eight and a part of one), an eighth of 108 tiles each per XCD
     "wide_shares": ([16, 1200, 0, 48, 16, 0, 272, 16, 528, 16, 32], 1152, 2944),
     "large_skewed": ([6000, 128, 0, 272], 4096, 4096),
-    # wide outputs (at least 3584 columns) and half a tile of them, at the small tiles' last sizes
     "large_uniform": ([1024, 912, 1040, 1024], 4096, 4096),
+    # (819 tokens per expert: half a tile of columns, at the small tiles' last sizes)
     "large_odd_columns": ([1024, 912, 0, 1040, 1024], 2048, 1408),
-    # two 256 x 128 tiles per CU; nine experts with between two and three of them, so 128 x 128
-    "one_round_wide": ([640, 528, 720, 672], 2048, 2048),
-    "second_round_short": ([256, 16, 0, 272, 128, 400, 32, 512, 144], 1024, 2048),
-    # 256 x 256 tiles in XCD blocks, and packed where the column tiles do not divide by four
-    "large_blocks": ([1152, 1040, 1168, 1248], 4096, 4096),
+    # 128 x 128 tiles, several per workgroup, for nine experts
+    "short_nine_experts": ([256, 16, 0, 272, 128, 400, 32, 512, 144], 1024, 2048),
+    # 256 x 256 tiles for few tokens, where the output is large; and packed where the column tiles do
+    # not divide by four
+    "large_short": ([912, 640, 912, 720, 896, 0, 1040, 784], 7168, 2048),
     "large_packed": ([1152, 1408, 0, 1168, 1536], 2048, 1408),
 }
 

@@ -104,9 +104,6 @@ FPROP, DGRAD, WGRAD = 0, 1, 2
 
 
 @pytest.mark.parametrize("mode,E,M_cap,N,K,small", [
-    # groups of whole tiles: the large tiles' count is the rows', with no share for partial ones
-    (FPROP, 8, 8 * 512, 4096, 7168, 0),        # 97 / 148
-    (FPROP, 16, 16 * 512, 2048, 2048, 0),      # 39 / 52
     (FPROP, 16, 16 * 384, 2048, 2048, 0),      # 34 / 40
     (FPROP, 16, 16 * 192, 2048, 2048, 128),    # 37 / 31
     (FPROP, 16, 16 * 256, 2048, 2048, 128),    # 40 / 32
@@ -133,17 +130,19 @@ FPROP, DGRAD, WGRAD = 0, 1, 2
     (FPROP, 32, 32 * 16, 7168, 2048, 64),      # 106 / 90
     (FPROP, 8, 8 * 96, 4096, 7168, 128),       # 80 / 57
     (WGRAD, 32, 32 * 768, 7168, 2048, 0),      # 583 / 613
-    (WGRAD, 64, 64 * 766, 2816, 2048, 0),      # 474 / 510
+    (WGRAD, 32, 24064, 7168, 2048, 0),         # 10000 tokens x 2: 561 / 610
     (WGRAD, 64, 64 * 768, 7168, 2048, 0),      # 1158 / 1229
-    (WGRAD, 64, 64 * 768, 1024, 1024, 0),      # 96 / 99
-    (WGRAD, 8, 8 * 4096, 1024, 1280, 0),       # 56 / 70
+    (WGRAD, 32, 32 * 512, 7168, 2048, 128),    # 509 / 512
+    (WGRAD, 32, 32 * 384, 7168, 2048, 128),    # 467 / 436
+    (WGRAD, 32, 32 * 640, 4096, 2560, 128),    # 414 / 407
+    (WGRAD, 6, 19328, 1024, 1536, 128),        # 6408 tokens x 3, skewed: 77 / 60
     (WGRAD, 8, 8 * 4096, 640, 1024, 128),      # 60 / 44
+    (WGRAD, 18, 20864, 2048, 128, 128),        # 2309 tokens x 8, skewed: 40 / 26
     (WGRAD, 64, 64 * 384, 2816, 2048, 128),    # 383 / 344
     (WGRAD, 64, 64 * 768, 2048, 1408, 128),    # 262 / 246
     (WGRAD, 16, 16 * 768, 2816, 2048, 128),    # 131 / 122
-    (WGRAD, 32, 32 * 512, 7168, 2048, 128),    # 509 / 512
-    (WGRAD, 32, 32 * 1024, 4096, 7168, 128),   # 1358 / 1226
-    (WGRAD, 32, 32 * 1280, 4096, 7168, 0),     # 1509 / 1405, skewed 1443 / 1483
+    (WGRAD, 32, 32 * 768, 4096, 7168, 128),    # 1212 / 1050
+    (WGRAD, 11, 11136, 3072, 5632, 0),         # 1374 tokens x 7, skewed: 273 / 326
 ])
 def test_tile_shape_choice(host_lib, mode, E, M_cap, N, K, small):
     args = [ctypes.c_int64(v) for v in (M_cap, N, K, 256)]
@@ -151,18 +150,16 @@ def test_tile_shape_choice(host_lib, mode, E, M_cap, N, K, small):
 
 
 @pytest.mark.parametrize("E,M_cap,N,K,wide", [
-    (4, 4 * 512, 2048, 2048, True),      # 128 x 128 tiles 28 us, 256 x 128 ones 23 (256 x 256: 25)
-    (16, 16 * 768, 1024, 1024, True),    # 35, 28 (31)
-    (15, 15 * 768, 1024, 2048, True),    # 56, 46 (48)
-    (12, 12 * 512, 1024, 2048, True),    # 37, 33
-    (32, 32 * 512, 4096, 7168, True),    # 1024, 920
+    (32, 32 * 512, 4096, 7168, True),    # 128 x 128 tiles 1024 us, 256 x 128 ones 920
+    (16, 16 * 640, 2048, 2048, True),    # 82, 69
+    (43, 21760, 2816, 256, False),       # skewed: 93, 148
+    (15, 10496, 512, 3840, False),       # skewed: 77, 112
     (8, 8 * 512, 1024, 1024, False),     # 17, 19
-    (8, 8 * 256, 768, 2048, False),      # 18, 19
-    (9, 9 * 512, 1024, 2048, False),     # 27, 30
-    (10, 10 * 256, 1024, 2048, False)])  # 23, 25
+    (28, 18304, 768, 384, False),        # skewed: 31, 46
+    (35, 35 * 128, 512, 1792, False)])   # 19 tokens: 28, 30
 def test_wgrad_small_tile_choice(host_lib, E, M_cap, N, K, wide):
-    args = [ctypes.c_int64(v) for v in (M_cap, N, K, 256)]
-    assert host_lib.tile_rule(WGRAD, E, *args) == 128
+    args = [ctypes.c_int64(v) for v in (N, K, 256)]
+    assert host_lib.tile_rule(WGRAD, E, ctypes.c_int64(M_cap), *args) == 128
     assert host_lib.tile_rule_wide(E, *args) == wide
 
 

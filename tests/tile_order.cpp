@@ -52,8 +52,6 @@ extern "C" long tile_order_walk(int E, const int* offsets, int m_cap, int n_pt, 
 extern "C" int tile_rule(int mode, int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus) {
   return ff8::small_gemm_tile((ff8::GemmMode)mode, E, M_cap, N, K, cus);
 }
-extern "C" int tile_rule_wide(int E, int64_t M_cap, int64_t N, int64_t K, int64_t cus) {
-  return ff8::wgrad_wide(E, M_cap, N, K, cus);
-}
+extern "C" int tile_rule_wide(int E, int64_t N, int64_t K, int64_t cus) { return ff8::wgrad_wide(E, N, K, cus); }
 extern "C" int tile_per_cu(int per_cu, int lds) { return ff8::small_per_cu(per_cu, lds); }
 extern "C" int route_launch_count(int64_t T, int k, int E, int align) { return ff8::route_launches(T, k, E, align); }
