@@ -79,8 +79,9 @@ __host__ __device__ __forceinline__ int order_blocks(int n_pt, int n_qg, bool pa
 // Whether packing saves a sweep over the XCDs, or half of one where the last can be split.  Where it
 // does not, the blocks' tiles stay together and spread over more XCDs (us, packed / blocks: 16 experts
 // of 450 rows, 1536 x 4096, fprop 60 / 56; 8 of 700 rows, 1408 x 2048, 37 / 34; wgrad of 8 experts of
-// 1024 x 640, 1100 tokens 29 / 26).  Over 540 products of odd widths packing gains 8% on average, by
-// this rule 9%.
+// 1024 x 640, 1100 tokens 29 / 26; but under skewed routing wgrad's sweeps are as long as their longest
+// tiles, and packing can spread those better: 8 of 2048 x 2560, 1100 tokens, Zipf(1.2) 89 / 122).  Over
+// 539 products of odd widths packing gains 8% on average, by this rule 9%.
 __host__ __device__ __forceinline__ bool packing_saves(int n_pt, int n_qg, bool split) {
   const int chunks = order_blocks(n_pt, n_qg, true), rest = chunks & 7;
   const int halves = 2 * (chunks >> 3) + (rest == 0 ? 0 : split && rest <= 4 ? 1 : 2);
@@ -93,7 +94,7 @@ __host__ __device__ __forceinline__ bool packing_saves(int n_pt, int n_qg, bool 
 // kPack (p tiles not a multiple of kBP), packed: every third or so block would be cut by the p edge
 // and leave its XCD a part of the work, so the blocks' tiles are packed into chunks of 32 in block
 // order, and blk is a chunk; every chunk but the last is full.  64 experts of 1024 rows, 2048 x
-// 1408 (6 p tiles): dgrad 254 -> 220 us, wgrad 364 -> 310.  With whole blocks only, the longer
+// 1408 (6 p tiles): dgrad 236 -> 200 us, wgrad 371 -> 302.  With whole blocks only, the longer
 // lookup between two tiles costs 1-2%, so those keep the short one.
 template <int MODE, bool kPack>
 __host__ __device__ __forceinline__ bool decode_tile(const GemmArgs& g, const int* cum, const int* off, int n_qg,
